@@ -59,31 +59,25 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 // max(clamp(q, a, b), zp) = clamp(q, max(a, zp), max(b, zp)).
 struct Epi3 {
   float lo, hi;
-  int32_t mult, shift, qlo, qhi, zp;
+  double scale;  // int8: multiplier / 2^shift
+  RqRange range;
+  int32_t zp;
 };
 __device__ __forceinline__ Epi3 make_epi3(int act, const Requant& rq) {
   Epi3 e;
   e.lo = act == ACT_NONE ? -__builtin_huge_valf() : 0.0f;
   e.hi = act == ACT_RELU6 ? 6.0f : __builtin_huge_valf();
-  e.mult = rq.mult;
-  e.shift = rq.shift;
+  e.scale = rq_scale(rq.mult, rq.shift);
+  e.range = rq_range(rq, act);  // (int8 ReLU6: its 6 is qmax)
   e.zp = rq.zp;
-  e.qlo = act != ACT_NONE ? max(rq.qmin, rq.zp) : rq.qmin;  // int8 ReLU6: its 6 is qmax
-  e.qhi = act != ACT_NONE ? max(rq.qmax, rq.zp) : rq.qmax;
   return e;
 }
 __device__ __forceinline__ float epi_f(float v, const Epi3& e) { return __builtin_amdgcn_fmed3f(v, e.lo, e.hi); }
 // (the multiplier and shift of the value's channel: the stage's, or per-channel ones)
 __device__ __forceinline__ int32_t epi_q(int32_t acc, int32_t mult, int32_t shift, const Epi3& e) {
-  const int64_t t = (int64_t)acc * mult;
-  const int64_t half = ((int64_t)1 << shift) >> 1;
-  const int64_t rnd = shift > 0 ? half - 1 + ((t >> shift) & 1) : 0;
-  int64_t q = ((t + rnd) >> shift) + e.zp;
-  q = q < e.qlo ? e.qlo : q;
-  q = q > e.qhi ? e.qhi : q;
-  return (int32_t)q;
+  return rq_round(acc, rq_scale(mult, shift), e.range) + e.zp;
 }
-__device__ __forceinline__ int32_t epi_i(int32_t acc, const Epi3& e) { return epi_q(acc, e.mult, e.shift, e); }
+__device__ __forceinline__ int32_t epi_i(int32_t acc, const Epi3& e) { return rq_round(acc, e.scale, e.range) + e.zp; }
 // A per-channel shift as the first-generation kernels take it: clamped to [0, 62].
 __device__ __forceinline__ int32_t pc_shift(uint32_t s) { return min(max((int32_t)s, 0), 62); }
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
@@ -586,14 +580,21 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
             if (pc_dw) {
               // this lane's CPL channels of chunk s: multipliers, then (512 bytes on) shifts
               const char* pm = buf + lay.bias_off + 2048 + (s * CB + g * CPL) * 4;
-              // One value at a time: each value's input is released by the previous
-              // result (a wave issues its vector instructions in order, so the chain costs
-              // no issue slots), which keeps the 64-bit temporaries of one value live
-              // instead of those of all NB x CPL.
-              int32_t tok = 0;
+              // Four values at a time: a group's scales are released by the previous
+              // group's result, which keeps one group's doubles live instead of those of
+              // all NB x CPL values (unchained, they spill; value by value, each waits for
+              // the four dependent instructions of the one before).
+              uint32_t tok = 0;
 #pragma unroll
               for (int j = 0; j < 4; ++j) {
                 const u32x4 mv = *(const u32x4*)(pm + 16 * j), sv = *(const u32x4*)(pm + 512 + 16 * j);
+                double sc[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  int32_t m = (int32_t)mv[e];
+                  asm volatile("" : "+v"(m) : "v"(tok));
+                  sc[e] = rq_scale(m, pc_shift(sv[e]));
+                }
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
                   uint32_t wv = 0;
@@ -601,9 +602,9 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
                   for (int e = 0; e < 4; ++e) {
                     int32_t v = dacc[b][4 * j + e];
                     asm volatile("" : "+v"(v) : "v"(tok));
-                    tok = epi_q(v, (int32_t)mv[e], pc_shift(sv[e]), ep_dw);
-                    wv |= ((uint32_t)tok & 0xffu) << (8 * e);
+                    wv |= ((uint32_t)(rq_round(v, sc[e], ep_dw.range) + ep_dw.zp) & 0xffu) << (8 * e);
                   }
+                  tok = wv;
                   bop[b][j] = wv;
                 }
               }

@@ -55,24 +55,6 @@ __device__ __forceinline__ u32x4 load_slot4(rsrc_t r, uint32_t row_off, int off,
   return v;
 }
 
-// int8 epilogue with an output zero point: round half to even, add zp, clamp to
-// [qlo, qhi] (which hold ReLU's floor at zp, see zp_epi).
-__device__ __forceinline__ int32_t epi_i_zp(int32_t acc, const Epi3& e, int32_t zp) {
-  const int64_t t = (int64_t)acc * e.mult;
-  const int64_t half = ((int64_t)1 << e.shift) >> 1;
-  const int64_t rnd = e.shift > 0 ? half - 1 + ((t >> e.shift) & 1) : 0;
-  int64_t q = ((t + rnd) >> e.shift) + zp;
-  q = q < e.qlo ? e.qlo : q;
-  q = q > e.qhi ? e.qhi : q;
-  return (int32_t)q;
-}
-// The clamp range of a stage whose output has zero point zp: ReLU / ReLU6 floor at zp.
-__device__ __forceinline__ Epi3 zp_epi(int act, const Requant& rq) {
-  Epi3 e = make_epi3(act, rq);
-  e.qlo = act != ACT_NONE ? max(rq.qmin, rq.zp) : rq.qmin;
-  e.qhi = act != ACT_NONE ? max(rq.qmax, rq.zp) : rq.qmax;
-  return e;
-}
 // Sum of the 16 int8 codes of a 16-byte operand slot, added to acc.
 __device__ __forceinline__ int32_t sum_i8x16(const u32x4& v, int32_t acc) {
 #pragma unroll
@@ -103,16 +85,6 @@ struct Mid4<TI8> {
     for (int v = 0; v < 4; ++v) {
       const int32_t s = acc[v];
       w |= ((uint32_t)epi_i(s + b[v], e) & 0xffu) << (8 * v);
-    }
-    slot[t] = w;
-  }
-  __device__ static __forceinline__ void put_zp(u32x4& slot, int t, const i32x4& acc, const int32_t (&b)[4],
-                                                const Epi3& e, int32_t zp) {
-    uint32_t w = 0;
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int32_t s = acc[v];
-      w |= ((uint32_t)epi_i_zp(s + b[v], e, zp) & 0xffu) << (8 * v);
     }
     slot[t] = w;
   }
@@ -154,16 +126,6 @@ __device__ __forceinline__ void store4_out(char* p, const typename DT::AccV& acc
     *(u32x4*)p = u32x4{__float_as_uint(epi_f(s0 + b[0], e)), __float_as_uint(epi_f(s1 + b[1], e)),
                        __float_as_uint(epi_f(s2 + b[2], e)), __float_as_uint(epi_f(s3 + b[3], e))};
   }
-}
-
-// int8 output of four consecutive channels with an output zero point.
-__device__ __forceinline__ void store4_out_zp(char* p, const i32x4& acc, const int32_t (&b)[4], const Epi3& e,
-                                              int32_t zp) {
-  const int32_t s0 = acc[0], s1 = acc[1], s2 = acc[2], s3 = acc[3];
-  *(uint32_t*)p = ((uint32_t)epi_i_zp(s0 + b[0], e, zp) & 0xffu) |
-                  (((uint32_t)epi_i_zp(s1 + b[1], e, zp) & 0xffu) << 8) |
-                  (((uint32_t)epi_i_zp(s2 + b[2], e, zp) & 0xffu) << 16) |
-                  ((uint32_t)epi_i_zp(s3 + b[3], e, zp) << 24);
 }
 
 // VEC: every operand row is a 16-byte aligned multiple of 16 bytes (x, both weight
@@ -213,7 +175,7 @@ __global__ __launch_bounds__(256) void k_pwpw4(KArgs a) {
 #pragma unroll
     for (int u = 0; u < CT; ++u) acc2[pb][u] = AccV{0, 0, 0, 0};
 
-  const Epi3 e1 = ZP ? zp_epi(a.act[0], a.rq[0]) : make_epi3(a.act[0], a.rq[0]);
+  const Epi3 e1 = make_epi3(a.act[0], a.rq[0]);
   [[maybe_unused]] int32_t rs2[CT];  // ZP: partial row sums of the second weights (this wave's chunks)
   if constexpr (ZP) {
 #pragma unroll
@@ -285,7 +247,7 @@ __global__ __launch_bounds__(256) void k_pwpw4(KArgs a) {
 #pragma unroll
         for (int s = 0; s < KS; ++s) mma16(DT(), acc1, o.a1[t][s], xb[pb][s]);
         if constexpr (ZP)
-          Mid4<DT>::put_zp(mid, t, acc1, b1z[t], e1, a.rq[0].zp);
+          Mid4<DT>::put(mid, t, acc1, b1z[t], e1);
         else
           Mid4<DT>::put(mid, t, acc1, o.b1[t], e1);
       }
@@ -329,7 +291,7 @@ __global__ __launch_bounds__(256) void k_pwpw4(KArgs a) {
       }
     }
   }
-  const Epi3 e2 = ZP ? zp_epi(a.act[1], a.rq[1]) : make_epi3(a.act[1], a.rq[1]);
+  const Epi3 e2 = make_epi3(a.act[1], a.rq[1]);
   char* y = (char*)a.y;
   // final epilogue of output tile u of pixel block pb: lane (pixel r16, group g) holds
   // output channels 16u + 4g + [0, 4)
@@ -340,10 +302,7 @@ __global__ __launch_bounds__(256) void k_pwpw4(KArgs a) {
     Acc b[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) b[q] = load_bias<DT>(a.b2, co + q);
-    if constexpr (ZP)
-      store4_out_zp(y + ((size_t)p * a.Co + co) * E, v, b, e2, a.rq[1].zp);
-    else
-      store4_out<DT>(y + ((size_t)p * a.Co + co) * E, v, b, e2);
+    store4_out<DT>(y + ((size_t)p * a.Co + co) * E, v, b, e2);
   };
 
   if (S > 1) {
