@@ -632,6 +632,22 @@ def chain_output_shape(desc):
     return (desc.n, c, h, w) if desc.layout == LAYOUT["nchw"] else (desc.n, h, w, c)
 
 
+def chain_workspace_bytes(desc):
+    """Device bytes of workspace that serve every plan of the chain (another objective's, a
+    tuned one): two buffers of the largest activation between any two layers. A given plan
+    needs fcm_chain_workspace_bytes, which is at most this."""
+    h, w, c, most = desc.h, desc.w, desc.c, 0
+    elt = {DTYPE["f32"]: 4, DTYPE["bf16"]: 2, DTYPE["i8"]: 1}[desc.dtype]
+    for i in range(desc.num_layers - 1):
+        L = desc.layers[i]
+        if L.kind == LAYER_KIND["pw"]:
+            c = L.c_out
+        else:
+            h, w = out_hw(h, w, L.k, L.stride, L.pad)
+        most = max(most, desc.n * h * w * c * elt)
+    return 2 * ((most + 255) // 256 * 256)
+
+
 class _ChainRun(Prepared):
     def __init__(self, fn, args, y, keep):
         super().__init__(fn, args, y)
@@ -640,7 +656,9 @@ class _ChainRun(Prepared):
 
 def chain_run(desc, plan, x, weights, biases=None, *, out=None, workspace=None, stream=None, prepare=False):
     """Run a planned chain: x the input tensor, weights/biases per layer (biases may be
-    None or hold None). The inter-group workspace is a torch allocation unless given."""
+    None or hold None). The inter-group workspace is a torch allocation unless given, large
+    enough for any plan of the chain. A prepared run points to the tensors passed in: the
+    caller keeps them alive."""
     torch = _torch()
     if len(weights) != desc.num_layers:
         raise ValueError("one weight tensor per layer")
@@ -652,7 +670,7 @@ def chain_run(desc, plan, x, weights, biases=None, *, out=None, workspace=None, 
         raise ValueError("out must be a contiguous %s tensor of shape %s" % (x.dtype, shape))
     nbytes = lib().fcm_chain_workspace_bytes(ctypes.byref(plan))
     if workspace is None and nbytes > 0:
-        workspace = torch.empty(nbytes, dtype=torch.uint8, device=x.device)
+        workspace = torch.empty(max(nbytes, chain_workspace_bytes(desc)), dtype=torch.uint8, device=x.device)
     if workspace is not None and workspace.numel() * workspace.element_size() < nbytes:
         raise ValueError("workspace smaller than fcm_chain_workspace_bytes")
     W = (ctypes.c_void_p * desc.num_layers)(*[t.data_ptr() for t in weights])
