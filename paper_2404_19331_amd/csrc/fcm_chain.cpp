@@ -153,8 +153,14 @@ fcm_status fcm_chain_plan(const fcm_chain_desc* chain, int32_t objective, const 
       }
       Opt o;
       o.op = op;
-      // groups run with the chain's activation buffers only: plans without split workspace
-      st = find_plan(op, &d, &H, &o.plan, kernel_set(op, &d), 0);
+      // groups run with the chain's activation buffers only: plans without split workspace.
+      // bf16: a sum that the PW->DW(->PW) kernels round differently (1e-5 of the values)
+      // travels through all layers that follow, and after MobileNetV2's 51 the outputs are
+      // 3.3e-3 off the other kernels', beyond the 2e-3 a bf16 chain is held to: bf16 chains
+      // keep the kernels that agree (batch 1: 287 us, with them 208 us; they can still be
+      // put in a chain plan explicitly). int8 chains are exact on any kernel.
+      const int kset = kernel_set(op, &d) | (d.dtype == FCM_BF16 ? KSET_SAME_ROUNDING : 0);
+      st = find_plan(op, &d, &H, &o.plan, kset, 0);
       if (st != FCM_OK) {
         if (single) return st;
         continue;

@@ -19,7 +19,9 @@ fcm_status fail(fcm_status st, const std::string& msg);
 // kZpMaxTiles output tiles.
 // KSET_PC (per-channel requantisation): the first-generation kernels and the int8
 // persistent kernels only.
-enum { KSET_FIRST = 0, KSET_DMA = 1, KSET_REG = 2, KSET_ALL = 3, KSET_PC = 4 };
+// KSET_SAME_ROUNDING (a flag): not the PW->DW(->PW) kernels, whose sums round differently
+// from the other kernels' now and then.
+enum { KSET_FIRST = 0, KSET_DMA = 1, KSET_REG = 2, KSET_ALL = 3, KSET_PC = 4, KSET_SAME_ROUNDING = 8 };
 // The set an int8 descriptor's features allow: per-channel requantisation -> KSET_PC;
 // zero points -> KSET_REG; else all.
 int kernel_set(int op, const fcm_desc* d);

@@ -355,6 +355,33 @@ FCM_HD inline Lds6 lds6(int mode, int K, int S, int TH, int TW, int ci, int cm, 
   return L;
 }
 
+// PW->DW(->PW) kernels (k_ir8, host and device): LDS bytes. The haloed window [position][the
+// input channels in whole 64 bytes] at pitch xp; per group of waves two buffers E of one
+// intermediate chunk [position][64 bytes] at pitch kPitchE8; the depthwise weights and the
+// biases of the first PW and the DW for the workgroup's mb intermediate channels, in whole
+// KiB. After the last chunk the groups' accumulators are exchanged over the same bytes.
+constexpr int kPitchE8 = 80;
+struct Lds8 {
+  int nqp, xp, e_off, e_buf, dww_off, b1_off, b2_off, total;
+};
+FCM_HD inline Lds8 lds8(int dt, int K, int S, int TH, int TW, int ci, int mb, int gw, int groups, int pb, int ct) {
+  Lds8 L{};
+  const int e = elt_size(dt), mbp = round_up(mb, 64 / e);
+  L.nqp = round_up(((TH - 1) * S + K) * ((TW - 1) * S + K), 16);
+  L.xp = round_up(ci * e, 64) + 16;
+  L.e_off = L.nqp * L.xp;
+  L.e_buf = L.nqp * kPitchE8;
+  L.dww_off = L.e_off + 2 * groups * L.e_buf;
+  L.b1_off = L.dww_off + round_up(mbp * K * K * e, 1024);
+  L.b2_off = L.b1_off + round_up(mbp * 4, 1024);
+  L.total = L.b2_off + round_up(mbp * 4, 1024);
+  const int red = (groups - 1) * gw * pb * ct * 1024;
+  if (red > L.total) L.total = red;
+  return L;
+}
+// Waves of a group: the 16-pixel blocks of a tile of p pixels, pb per wave.
+FCM_HD inline int waves8(int p, int pb) { return p <= 16 * pb ? 1 : (p <= 32 * pb ? 2 : 4); }
+
 // ---------------------------------------------------------------------------------
 // Kernel argument block (one struct for all families; unused fields ignored).
 // ---------------------------------------------------------------------------------
@@ -385,6 +412,8 @@ struct KArgs {
   int grid_cap;  // persistent kernels: at most this many workgroups (0 = no cap)
   const int32_t* rqc[3];  // int8 per-channel requantisation per stage ([2][channels]) or nullptr
   int zin[3];             // int8 zero point of each stage's input
+  int stride;             // depthwise stride (k_ir8; a template argument elsewhere)
+  int gw;                 // k_ir8: waves per group
 };
 
 // One compiled kernel instance and the tilings it implements.
@@ -414,11 +443,14 @@ struct Variant {
                     //    every channel of every stage in one workgroup
                     // 7: deep DW->PW kernels (bf16, 3x3): compile-time tile of at most 64
                     //    pixels, one compiled output-channel block
+                    // 8: PW->DW(->PW) NHWC kernels (bf16, int8): run-time tile of at most
+                    //    max_p pixels, 64-byte intermediate chunks
   int pitch = 0;    // gen 3: LDS window row pitch in pixels (window width must not exceed it)
   int ks = 1;       // gen 3: 64-byte channel chunks per item; gen 4: 64-byte k-steps of the
                     // first convolution held in registers (input channels <= 64 * ks bytes);
-                    // gen 5: LDS ring slots
-  int wc = 1;       // gen 5: waves across output channels (1, 2 or 4)
+                    // gen 5: LDS ring slots; gen 8: as gen 4
+  int wc = 1;       // gen 5: waves across output channels (1, 2 or 4); gen 8: 16-pixel
+                    // blocks per wave
   int kc = 1;       // gen 7: 32-channel chunks per item (1 or 2)
 };
 
@@ -444,6 +476,9 @@ const Variant* variants_v3_pw_i8(int* count);
 const Variant* variants_v3_dw_bf16(int* count);
 const Variant* variants_v3_dw_f32(int* count);
 const Variant* variants_v3_dw_i8(int* count);
+const Variant* variants_v8_bf16(int* count);
+const Variant* variants_v8_i8_k3(int* count);
+const Variant* variants_v8_i8_k5(int* count);
 const Variant* variants_v4_pwpw_i8(int* count);
 const Variant* variants_v4_pwpw_bf16(int* count);
 const Variant* variants_v4_pwpw_f32(int* count);

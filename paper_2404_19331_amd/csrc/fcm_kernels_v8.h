@@ -1,0 +1,443 @@
+// fcm_kernels_v8.h -- PW->DW and PW->DW->PW modules on NHWC, bf16 and int8 (gfx950).
+//
+// k_ir8<DT, K, KS, CT, PB>
+//   A workgroup computes one TH x TW output tile (run time) of one image. The intermediate
+//   channels go through it in chunks of MC = 64 bytes (one MFMA k-step of the last
+//   convolution): the first PW expands a chunk on the tile's haloed window into an LDS
+//   buffer E, the depthwise stage filters it, and the result is either stored (PW -> DW,
+//   CT = 0) or contracted into output accumulators that stay in registers
+//   (output-stationary, Sec. III-A OS-LWS). GW waves (1, 2 or 4) form a group; J groups of
+//   one workgroup take chunks j, j + J, ... and add their accumulators through LDS at the
+//   end, which keeps the chain of chunks short where a launch has few tiles.
+//
+//   Per chunk and wave:
+//   * PW1: the wave's 16-position tiles of the window (w, w + GW, ...). The window sits in
+//     LDS ([position][channel slots], staged once), the chunk's weight rows in A-operand
+//     registers, loaded a chunk ahead. The lane (position l % 16, group l / 16) collects
+//     its accumulators (bias as the MFMA's C operand), activation and cast into the 16-byte
+//     slot l / 16 of E's position: bf16 rows are taken in the order that makes the slot 8
+//     consecutive channels; int8 takes natural rows, byte 4t + v of slot s being channel
+//     16t + 4s + v. Positions outside the image are written as real 0 (the DW's padding,
+//     Sec. III-A PWDW_R).
+//   * one barrier (E is double buffered)
+//   * DW: lane = output pixel l % 16 of the wave's own 16-pixel blocks, slot l / 16.
+//     bf16: dot instructions on pairs of taps, weights broadcast within 16-lane rows by
+//     DPP (dw_channel7), each row holding its own slot's weights. int8: on the matrix
+//     cores. For slot s the A operand is diagonal, row m holding the weight of tap
+//     4 kk + l / 16 at byte m of the slot, zero elsewhere; the B operand is E's slot s at
+//     that tap's position. Row m of slot s is channel 16 (m / 4) + 4s + m % 4, so after the
+//     four slots the lane holds channels 16 (l / 16) .. + 15 of its pixel: 16 contiguous
+//     bytes to store, or the B operand of PW2. (Integer zeros cannot pick up a NaN or
+//     infinity of a neighbouring channel, so only int8 can use the diagonal form.)
+//   * PW2: the DW result is the MFMA's B operand without leaving the registers.
+//
+//   E and the window have a pitch of 16 bytes more than a multiple of 64, an odd number of
+//   16-byte units: 16 lanes at consecutive positions reach every LDS bank once.
+//
+//   What bounds it: the vector ALU (the epilogues of PW1 on the haloed window and of DW),
+//   then launch and the chain of chunks for small batches; LDS and the matrix cores are
+//   below half busy.
+#pragma once
+
+#include "fcm_kernels_v7.h"
+#include "fcm_kernels_v4.h"
+
+namespace fcm {
+
+constexpr int kMaxWaves8 = 8;
+
+// int8 requantisation of a stage: in single precision where that is exact, else in double
+// (rq_round). Single precision is exact for every int32 accumulator if the multiplier has
+// at most 24 bits (the scale is then a float and the fma's product exact) and the scale is
+// at least 2^-16: an accumulator beyond 2^24, which the conversion rounds, then lies
+// beyond the clamp. 12 SIMD cycles a value against 21.
+struct Rq8 {
+  bool f32;
+  float s, lo, hi;
+  double ds;
+  RqRange r;
+};
+__device__ __forceinline__ Rq8 make_rq8(const Requant& rq, int act) {
+  Rq8 e;
+  const int32_t am = rq.mult < 0 ? -rq.mult : rq.mult;
+  e.f32 = am > 0 && am <= (1 << 24) && (rq.shift <= 16 || ((int64_t)am << 16) >= ((int64_t)1 << rq.shift));
+  e.ds = rq_scale(rq.mult, rq.shift);
+  e.s = (float)e.ds;
+  e.r = rq_range(rq, act);
+  e.lo = 12582912.0f + (float)(e.r.lo - kRoundF64);  // 1.5 * 2^23
+  e.hi = 12582912.0f + (float)(e.r.hi - kRoundF64);
+  return e;
+}
+// Four results as packed bytes.
+__device__ __forceinline__ uint32_t rq8x4(const i32x4& acc, const Rq8& e) {
+  uint32_t q[4];
+  if (e.f32) {  // (uniform)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int32_t s = acc[v];
+      q[v] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf((float)s, e.s, 12582912.0f), e.lo, e.hi));
+    }
+  } else {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int32_t s = acc[v];
+      q[v] = (uint32_t)rq_round(s, e.ds, e.r);
+    }
+  }
+  return __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
+}
+
+// Two float results as packed bf16. Without an activation the value passes as it is (a
+// median with infinite ends would turn a NaN into one of them).
+struct EpiF8 {
+  bool none;
+  float lo, hi;
+};
+__device__ __forceinline__ EpiF8 make_epif8(int act) {
+  return EpiF8{act == ACT_NONE, 0.0f, act == ACT_RELU6 ? 6.0f : __builtin_huge_valf()};
+}
+__device__ __forceinline__ uint32_t bf16x2_8(float v0, float v1, const EpiF8& e) {
+  if (e.none) return pack_bf16x2(v0, v1);  // (uniform)
+  return pack_bf16x2(__builtin_amdgcn_fmed3f(v0, e.lo, e.hi), __builtin_amdgcn_fmed3f(v1, e.lo, e.hi));
+}
+
+// 16 bytes at voff (+ soff) of a row-major matrix whose rows are multiples of 16 bytes
+// (vec) or of 4 bytes; nb: bytes of the row left from voff on (the rest reads as zero).
+__device__ __forceinline__ u32x4 load_row8(rsrc_t r, bool vec, uint32_t voff, uint32_t soff, int nb) {
+  if (vec) return __builtin_amdgcn_raw_buffer_load_b128(r, nb > 0 ? voff : kOob, soff, 0);
+  u32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    v[e] = __builtin_amdgcn_raw_buffer_load_b32(r, 4 * e < nb ? voff + 4 * e : kOob, soff, 0);
+  return v;
+}
+
+template <class DT, int K, int KS, int CT, int PB>
+__global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
+  extern __shared__ __align__(16) char smem[];
+  constexpr bool I8 = std::is_same<DT, TI8>::value;
+  static_assert(I8 || K == 3, "bf16: 3x3");
+  using AccV = typename DT::AccV;
+  constexpr int E = DT::ELT, MC = 64 / E, TPC = 4 / E, CPG = 16 / E;
+  constexpr int KK = K * K, NKK = (KK + 3) / 4;
+  constexpr int EP = kPitchE8;
+  constexpr int NU = CT > 0 ? CT : 1;
+
+  const int S = a.stride, TW = a.TW, P = a.TH * TW;
+  const int IH = (a.TH - 1) * S + K, IW = (TW - 1) * S + K, Q = IH * IW;
+  const int J = a.splits, GW = a.gw;
+  const int MB = CT > 0 ? a.Cm : a.COB;  // intermediate channels of this workgroup
+  const Lds8 lay = lds8(dtype_id<DT>(), K, S, a.TH, TW, a.Ci, MB, GW, J, PB, CT);
+  const int ci_b = a.Ci * E, cm_b = a.Cm * E;
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int r16 = lane & 15, g = lane >> 4;
+  const int nw = GW * J;
+  const int j = wave / GW, w = wave % GW;
+
+  // ---- this workgroup's tile ----
+  const int lid = xcd_remap(blockIdx.x, gridDim.x);
+  const int cb = CT > 0 ? 0 : lid % a.n_cb;
+  int t = CT > 0 ? lid : lid / a.n_cb;
+  const int tx = t % a.tiles_x;
+  t /= a.tiles_x;
+  const int ty = t % a.tiles_y, n = t / a.tiles_y;
+  const int oy0 = ty * a.TH, ox0 = tx * TW;
+  const int iy0 = oy0 * S - a.pad, ix0 = ox0 * S - a.pad;
+  const int cm0 = cb * MB;                       // first intermediate channel
+  const int mb = min(MB, a.Cm - cm0);            // of this workgroup
+  const int nch = ceil_div(mb, MC);
+
+  // ---- depthwise weights and both biases of the workgroup's channels: flat copies ----
+  {
+    const rsrc_t rd = make_rsrc((const char*)a.w2 + (size_t)cm0 * KK * E, (uint32_t)(mb * KK * E));
+    const rsrc_t r1 = make_rsrc(a.b1 ? (const char*)a.b1 + (size_t)cm0 * 4 : (const char*)a.w1, a.b1 ? mb * 4u : 0u);
+    const rsrc_t r2 = make_rsrc(a.b2 ? (const char*)a.b2 + (size_t)cm0 * 4 : (const char*)a.w1, a.b2 ? mb * 4u : 0u);
+    const int nd = (lay.b1_off - lay.dww_off) >> 10, nb = (lay.b2_off - lay.b1_off) >> 10;
+    for (int i = wave; i < nd + 2 * nb; i += nw) {
+      if (i < nd)
+        dma16(rd, smem + lay.dww_off + i * 1024, (uint32_t)(i * 1024 + lane * 16));
+      else if (i < nd + nb)
+        dma16(r1, smem + lay.b1_off + (i - nd) * 1024, (uint32_t)((i - nd) * 1024 + lane * 16));
+      else
+        dma16(r2, smem + lay.b2_off + (i - nd - nb) * 1024, (uint32_t)((i - nd - nb) * 1024 + lane * 16));
+    }
+  }
+  // ---- first chunk's PW1 weights (A operands), a chunk ahead of their use ----
+  const rsrc_t rw1 = make_rsrc(a.w1, (uint32_t)(a.Cm * ci_b));
+  uint32_t aoff[KS];
+  int anb[KS];
+#pragma unroll
+  for (int s = 0; s < KS; ++s) {
+    const int row = I8 ? r16 : CPG * (r16 >> 2) + (r16 & 3);
+    aoff[s] = (uint32_t)(row * ci_b + 64 * s + 16 * g);
+    anb[s] = ci_b - (64 * s + 16 * g);
+  }
+  u32x4 a1[TPC][KS];
+  auto load_a1 = [&](int c) {
+#pragma unroll
+    for (int tt = 0; tt < TPC; ++tt) {
+      const uint32_t so = (uint32_t)((cm0 + c * MC + (I8 ? 16 : 4) * tt) * ci_b);
+#pragma unroll
+      for (int s = 0; s < KS; ++s) a1[tt][s] = load_row8(rw1, a.vec_w1, aoff[s], so, anb[s]);
+    }
+  };
+  if (j < nch) load_a1(j);
+
+  // ---- the haloed window: [position][16-byte slots], zero outside the image and beyond
+  // the input channels ----
+  {
+    const size_t img = (size_t)a.H * a.W * ci_b;
+    const rsrc_t rx = make_rsrc((const char*)a.x + (size_t)n * img, (uint32_t)img);
+    const int nsl = 4 * ceil_div(ci_b, 64), items = lay.nqp * nsl, step = 64 * nw;
+    constexpr int B = 4;
+    for (int i0 = threadIdx.x; i0 < items; i0 += step * B) {
+      u32x4 v[B];
+      int dst[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b) {
+        const int i = i0 + b * step;
+        const int pos = i / nsl, sl = i - pos * nsl;
+        const int qy = pos / IW, qx = pos - qy * IW;
+        const int gy = iy0 + qy, gx = ix0 + qx;
+        const bool ok = pos < Q && (unsigned)gy < (unsigned)a.H && (unsigned)gx < (unsigned)a.W;
+        dst[b] = i < items ? pos * lay.xp + sl * 16 : -1;
+        v[b] = load_row8(rx, a.vec_x, (uint32_t)((gy * a.W + gx) * ci_b + sl * 16), 0u, ok ? ci_b - sl * 16 : 0);
+      }
+#pragma unroll
+      for (int b = 0; b < B; ++b)
+        if (dst[b] >= 0) *(u32x4*)(smem + dst[b]) = v[b];
+    }
+  }
+
+  // ---- the wave's window tiles and output pixels ----
+  const int nqt = lay.nqp >> 4;
+  uint32_t inside = 0;  // bit i: this lane's position of the wave's i-th tile lies in the image
+  for (int i = 0, qt = w; qt < nqt; ++i, qt += GW) {
+    const int pos = qt * 16 + r16;
+    const int qy = pos / IW, qx = pos - qy * IW;
+    const bool ok = pos < Q && (unsigned)(iy0 + qy) < (unsigned)a.H && (unsigned)(ix0 + qx) < (unsigned)a.W;
+    inside |= (ok ? 1u : 0u) << i;
+  }
+  int ebase[PB], opix[PB];  // E position of the pixel's first tap; output pixel or -1
+#pragma unroll
+  for (int b = 0; b < PB; ++b) {
+    const int p = (b * GW + w) * 16 + r16, pc = min(p, P - 1);
+    const int py = pc / TW, px = pc - py * TW;
+    ebase[b] = (py * S * IW + px * S) * EP + (I8 ? 0 : 16 * g);
+    opix[b] = p < P && oy0 + py < a.Ho && ox0 + px < a.Wo ? ((oy0 + py) * a.Wo + ox0 + px) : -1;
+  }
+  [[maybe_unused]] int tko[NKK];  // int8: E offset of the lane group's tap of each k-step
+  [[maybe_unused]] uint32_t dmask[4];
+  if constexpr (I8) {
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      const int tap = min(4 * kk + g, KK - 1);
+      tko[kk] = ((tap / K) * IW + tap % K) * EP;
+    }
+#pragma unroll
+    for (int d = 0; d < 4; ++d) dmask[d] = (r16 >> 2) == d ? 0xffu << (8 * (r16 & 3)) : 0u;
+  }
+
+  AccV acc2[PB][NU];
+#pragma unroll
+  for (int b = 0; b < PB; ++b)
+#pragma unroll
+    for (int u = 0; u < NU; ++u) acc2[b][u] = AccV{0, 0, 0, 0};
+
+  const EpiF8 e1 = make_epif8(a.act[0]), e2 = make_epif8(a.act[1]);
+  const Rq8 q1 = make_rq8(a.rq[0], a.act[0]);
+  const Rq8 q2 = make_rq8(a.rq[1], a.act[1]);
+  const rsrc_t rw3 = make_rsrc(CT > 0 ? a.w3 : a.w1, CT > 0 ? (uint32_t)(a.Co * cm_b) : 0u);
+  const uint32_t a2off = (uint32_t)(r16 * cm_b + 16 * g);
+  const int nks = ceil_div(ci_b, 64);  // k-steps of PW1 (staged ones)
+
+  wait_vm_n<0>();
+  wait_lgkm0();
+  barrier3();
+
+  const int niter = ceil_div(nch, J);
+  for (int it = 0; it < niter; ++it) {
+    const int c = j + J * it;
+    const bool active = c < nch;
+    char* eb = smem + lay.e_off + (2 * j + (it & 1)) * lay.e_buf;
+    const int m0 = c * MC;  // within the workgroup's channels
+    u32x4 a2[NU];
+    if (active) {
+      if constexpr (CT > 0) {
+        const uint32_t vo = m0 * E + 16 * g < cm_b ? a2off : kOob;
+#pragma unroll
+        for (int u = 0; u < CT; ++u)
+          a2[u] = __builtin_amdgcn_raw_buffer_load_b128(rw3, vo, (uint32_t)(u * 16 * cm_b + m0 * E), 0);
+      }
+      // ---- PW1 on the wave's window tiles ----
+      AccV b1[TPC];
+#pragma unroll
+      for (int tt = 0; tt < TPC; ++tt) {
+        const int ch = I8 ? m0 + 16 * tt + 4 * g : m0 + CPG * g + 4 * tt;
+        b1[tt] = *(const AccV*)(smem + lay.b1_off + ch * 4);
+      }
+      const char* xp = smem + (w * 16 + r16) * lay.xp + 16 * g;
+      char* ep = eb + (w * 16 + r16) * EP + 16 * g;
+#pragma unroll 2
+      for (int i = 0, qt = w; qt < nqt; ++i, qt += GW) {
+        AccV acc[TPC];
+#pragma unroll
+        for (int tt = 0; tt < TPC; ++tt) acc[tt] = b1[tt];
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+          if (s > 0 && s >= nks) break;  // (uniform; nothing is staged there)
+          const u32x4 xb = *(const u32x4*)(xp + 64 * s);
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt) mma16(DT{}, acc[tt], a1[tt][s], xb);
+        }
+        u32x4 o;
+        if constexpr (I8) {
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt) o[tt] = rq8x4(acc[tt], q1);
+        } else {
+#pragma unroll
+          for (int tt = 0; tt < TPC; ++tt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+              o[2 * tt + h] = bf16x2_8(acc[tt][2 * h], acc[tt][2 * h + 1], e1);
+        }
+        const bool in = (inside >> i) & 1u;
+#pragma unroll
+        for (int d = 0; d < 4; ++d) o[d] = in ? o[d] : 0u;
+        *(u32x4*)ep = o;
+        xp += GW * 16 * lay.xp;
+        ep += GW * 16 * EP;
+      }
+    }
+    wait_lgkm0();
+    barrier3();
+    if (active) {
+      if (c + J < nch) load_a1(c + J);
+      // ---- DW on the wave's pixel blocks, PW2 or the store ----
+      u32x4 d[PB];
+      if constexpr (I8) {
+        const char* wb = smem + lay.dww_off + (m0 + 16 * (r16 >> 2) + (r16 & 3)) * KK;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          AccV acc[PB];
+          const AccV bv = *(const AccV*)(smem + lay.b2_off + (m0 + 16 * g + 4 * s) * 4);
+#pragma unroll
+          for (int b = 0; b < PB; ++b) acc[b] = bv;
+#pragma unroll
+          for (int kk = 0; kk < NKK; ++kk) {
+            const int tap = 4 * kk + g;
+            uint32_t wt = *(const uint8_t*)(wb + 4 * s * KK + min(tap, KK - 1));
+            if (4 * kk + 3 >= KK) wt = tap < KK ? wt : 0u;
+            wt = __builtin_amdgcn_perm(wt, wt, 0u);  // the byte in all four places
+            const u32x4 av = {wt & dmask[0], wt & dmask[1], wt & dmask[2], wt & dmask[3]};
+#pragma unroll
+            for (int b = 0; b < PB; ++b) mma16(DT{}, acc[b], av, *(const u32x4*)(eb + ebase[b] + tko[kk] + 16 * s));
+          }
+#pragma unroll
+          for (int b = 0; b < PB; ++b) d[b][s] = rq8x4(acc[b], q2);
+        }
+      } else {
+        const int wo = r16 < 9 ? lay.dww_off + (m0 + 8 * g) * 18 + 16 * r16
+                               : lay.b2_off + (m0 + 8 * g) * 4 + 16 * (r16 == 10 ? 1 : 0);
+        const u32x4 wv = *(const u32x4*)(smem + wo);
+#pragma unroll
+        for (int b = 0; b < PB; ++b) {
+          const char* xb = eb + ebase[b];
+          u32x4 xv[9];
+#pragma unroll
+          for (int ky = 0; ky < 3; ++ky)
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) xv[3 * ky + kx] = *(const u32x4*)(xb + (ky * IW + kx) * EP);
+          float acc[8];
+          acc[0] = bcast7<9>(wv[0]);
+          acc[1] = bcast7<9>(wv[1]);
+          acc[2] = bcast7<9>(wv[2]);
+          acc[3] = bcast7<9>(wv[3]);
+          acc[4] = bcast7<10>(wv[0]);
+          acc[5] = bcast7<10>(wv[1]);
+          acc[6] = bcast7<10>(wv[2]);
+          acc[7] = bcast7<10>(wv[3]);
+          static_for7<0, 8>([&](auto jc) {
+            constexpr int JJ = decltype(jc)::value;
+            dw_channel7<JJ>(acc[JJ], xv, wv);
+          });
+#pragma unroll
+          for (int q = 0; q < 4; ++q) d[b][q] = bf16x2_8(acc[2 * q], acc[2 * q + 1], e2);
+        }
+      }
+      if constexpr (CT > 0) {
+#pragma unroll
+        for (int u = 0; u < CT; ++u) {
+#pragma unroll
+          for (int b = 0; b < PB; ++b) mma16(DT{}, acc2[b][u], a2[u], d[b]);
+        }
+      } else {
+        const int ch = m0 + CPG * g;
+#pragma unroll
+        for (int b = 0; b < PB; ++b)
+          if (opix[b] >= 0 && ch < mb)
+            *(u32x4*)((char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Cm + cm0 + ch) * E) = d[b];
+      }
+    }
+  }
+
+  if constexpr (CT > 0) {
+    if (J > 1) {  // the groups' sums, in group order
+      wait_lgkm0();
+      barrier3();
+      AccV* red = (AccV*)smem;
+      if (j > 0) {
+#pragma unroll
+        for (int b = 0; b < PB; ++b)
+#pragma unroll
+          for (int u = 0; u < CT; ++u) red[(((wave - GW) * PB + b) * CT + u) * 64 + lane] = acc2[b][u];
+      }
+      wait_lgkm0();
+      barrier3();
+      if (j > 0) return;
+      for (int jj = 1; jj < J; ++jj)
+#pragma unroll
+        for (int b = 0; b < PB; ++b)
+#pragma unroll
+          for (int u = 0; u < CT; ++u)
+            acc2[b][u] += red[((((jj - 1) * GW + w) * PB + b) * CT + u) * 64 + lane];
+    }
+    const EpiF8 e3 = make_epif8(a.act[2]);
+    const Rq8 q3 = make_rq8(a.rq[2], a.act[2]);
+#pragma unroll
+    for (int u = 0; u < CT; ++u) {
+      const int co = 16 * u + 4 * g;
+      if (co >= a.Co) continue;
+      AccV bb;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bb[q] = load_bias<DT>(a.b3, co + q);
+#pragma unroll
+      for (int b = 0; b < PB; ++b) {
+        const AccV v = acc2[b][u] + bb;
+        char* y = (char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Co + co) * E;
+        if constexpr (I8) {
+          const uint32_t o = rq8x4(v, q3);
+          if (opix[b] >= 0) *(uint32_t*)y = o;
+        } else {
+          const u32x2 o = {bf16x2_8(v[0], v[1], e3), bf16x2_8(v[2], v[3], e3)};
+          if (opix[b] >= 0) *(u32x2*)y = o;
+        }
+      }
+    }
+  }
+}
+
+template <class DT, int K, int KS, int CT, int PB>
+int launch_ir8(const KArgs& a, int grid, void* stream) {
+  const void* fn = (const void*)k_ir8<DT, K, KS, CT, PB>;
+  const int lds = a.L.bytes;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return (int)e;
+  }
+  return launch_args(fn, grid, 64 * a.gw * a.splits, lds, stream, a);
+}
+
+}  // namespace fcm

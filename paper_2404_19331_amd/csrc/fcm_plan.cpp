@@ -303,6 +303,7 @@ bool variant_needs_alignment(int variant) {
 // tiles; with per-channel requantisation (KSET_PC) the int8 persistent kernels.
 static bool in_set(const Variant& v, int kset) {
   if (v.gen < 2) return true;
+  if ((kset & KSET_SAME_ROUNDING) && v.gen == 8) return false;
   if (kset == KSET_PC) return v.gen == 3 && v.dtype == DT_I8;
   if (kset & KSET_DMA) return true;
   if (!(kset & KSET_REG)) return false;
@@ -376,6 +377,51 @@ static fcm_status evaluate_plan4(const Variant& v, const Geom& g, const fcm_hw_d
   return FCM_OK;
 }
 
+// Plan of the PW->DW(->PW) kernels: any tile of at most max_p output pixels, 64-byte
+// intermediate chunks; PW->DW may split the intermediate channels over workgroups in
+// blocks of whole chunks (co_block). splits: groups of waves of a workgroup sharing a
+// tile's chunks.
+static fcm_status evaluate_plan8(const Variant& v, const Geom& g, const fcm_hw_desc& hw, fcm_plan_t* p) {
+  const int e = g.elt, mc = 64 / e;
+  const bool last_pw = g.family == FAM_PWDWPW;
+  if (g.layout != FCM_NHWC) return fail(FCM_EUNSUPPORTED, "plan: the kernel needs NHWC");
+  if ((g.ci * e) % 4 || (g.cm * e) % 16 || (last_pw && g.co % 4))
+    return fail(FCM_EUNSUPPORTED, "plan: the kernel needs 4-byte input rows, 16-byte intermediate rows and output "
+                                  "channels in fours");
+  if (g.ci * e > 64 * v.ks || (last_pw && g.co > v.max_cob))
+    return fail(FCM_EUNSUPPORTED, "plan: channels exceed what the kernel variant holds in registers");
+  const int64_t lim = (int64_t)1 << 30;  // 32-bit buffer offsets with room for an out-of-range scalar part
+  if ((int64_t)g.h * g.w * g.ci * e >= lim || (int64_t)(g.cm + mc) * g.ci * e >= lim ||
+      (int64_t)(g.co + 16) * g.cm * e >= lim)
+    return fail(FCM_EUNSUPPORTED, "plan: tensor too large for the kernel");
+  const int TH = p->tile_h, TW = p->tile_w, P = TH * TW;
+  if (TH <= 0 || TW <= 0 || P > v.max_p) return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
+  const int64_t q = (int64_t)((TH - 1) * g.s + g.k) * ((TW - 1) * g.s + g.k);
+  const int gw = waves8(P, v.wc), groups = std::max(1, (int)p->splits);
+  if (q > 512 * gw) return fail(FCM_EUNSUPPORTED, "plan: window exceeds the kernel's position masks");
+  if (p->c_block != mc) return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
+  if (last_pw ? p->co_block != round_up(g.co, 16) : (p->co_block <= 0 || p->co_block % mc || p->co_block > round_up(g.cm, mc)))
+    return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
+  const int mb = last_pw ? g.cm : p->co_block;
+  if (gw * groups > 8 || groups > ceil_div(mb, mc) || (groups & (groups - 1)))
+    return fail(FCM_EUNSUPPORTED, "plan: 1, 2, 4 or 8 groups of at most eight waves and one chunk each");
+  const Lds8 L = lds8(g.dtype, g.k, g.s, TH, TW, g.ci, mb, gw, groups, v.wc, v.max_cob / 16);
+  if (L.total > hw.lds_per_wg) return fail(FCM_EUNSUPPORTED, "plan: tiling exceeds the LDS per workgroup");
+  const int64_t wgs = (int64_t)g.n * ceil_div(g.ho, TH) * ceil_div(g.wo, TW) * (last_pw ? 1 : ceil_div(g.cm, p->co_block));
+  if (wgs > 0x7fffffff) return fail(FCM_EUNSUPPORTED, "plan: grid too large");
+  const Bytes b = module_bytes(g, TH, TW, p->co_block);
+  p->waves = gw * groups;
+  p->depth = 0;
+  p->splits = groups;
+  p->lds_bytes = L.total;
+  p->workgroups = (int32_t)wgs;
+  p->bytes_ideal = b.ideal;
+  p->bytes_tiled = b.tiled;
+  p->bytes_paper = b.paper;
+  p->redundancy = b.redundancy;
+  return FCM_OK;
+}
+
 fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, fcm_plan_t* p) {
   (void)d;
   int nv = 0;
@@ -384,6 +430,7 @@ fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
   const Variant& v = vs[p->variant];
   if (!variant_matches(v, g)) return fail(FCM_EUNSUPPORTED, "plan: kernel variant does not implement this module");
   if (v.gen == 4) return evaluate_plan4(v, g, hw, p);
+  if (v.gen == 8) return evaluate_plan8(v, g, hw, p);
   int depth = v.gen == 3 ? p->depth : 0;
   const int lds = tiling_lds(v, g, p->tile_h, p->tile_w, p->c_block, p->co_block, hw.lds_per_wg, &depth);
   if (lds <= 0) return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
@@ -721,6 +768,38 @@ static double deep_time_estimate(const Variant& v, const Geom& g, const fcm_plan
   return kLaunch + std::max(cyc / kClock, (double)p.bytes_ideal / kRate);
 }
 
+// Time model of the PW->DW(->PW) kernels (gen 8), in seconds: the launch, then the chunks of
+// a workgroup one after another, each a fixed part (barrier, operand latency) and the
+// instructions of a wave (window tiles of PW1 with their epilogue, DW blocks, MFMAs), which
+// the waves sharing a SIMD stretch; plus the window's staging and the exchange of the
+// groups' accumulators; whole rounds of workgroups where they exceed the resident ones.
+// Fitted to 2660 timed plans of eleven block shapes (batch 1, 8, 32, both types and
+// modules, 3x3 and 5x5): within 0.85-1.16x for 80% of them; the chosen plan is within 4%
+// of the best timed one on average.
+static double ir_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
+  constexpr double kLaunch = 1.5e-6, kClock = 2.4e9, kStart = 6730.0, kIter = 1670.0, kAlone = 0.73, kShared = 0.306,
+                   kMfma = 81.0, kWave = 56.0, kExchange = 138.0, kStage = 490.0;
+  const bool i8 = g.elt == 1;
+  const double kTile = i8 ? 969.0 : 167.0, kBlock = i8 ? 159.0 : 872.0, kTaps = i8 ? 277.0 : 0.0;
+  const int mc = 64 / g.elt, gw = waves8(p.tile_h * p.tile_w, v.wc), groups = std::max(1, (int)p.splits);
+  const bool pw2 = g.family == FAM_PWDWPW;
+  const int mb = pw2 ? g.cm : std::min(p.co_block, g.cm);
+  const int q = ((p.tile_h - 1) * g.s + g.k) * ((p.tile_w - 1) * g.s + g.k);
+  const int ks = ceil_div(g.ci * g.elt, 64), nkk = ceil_div(g.k * g.k, 4);
+  const double nqt = ceil_div(ceil_div(q, 16), gw), ct = pw2 ? ceil_div(g.co, 16) : 0;
+  const double iters = ceil_div(ceil_div(mb, mc), groups), nw = gw * groups;
+  const double mfma = 4 / g.elt * ks * nqt + ct * v.wc + (i8 ? 4 * nkk * v.wc : 0);
+  const double valu = nqt * kTile + v.wc * kBlock + kTaps * (nkk - 3) + kMfma * mfma;
+  const int fit = std::min(hw.lds_per_cu / std::max(1, (int)p.lds_bytes), (int)(12 / nw));
+  const double per_cu = std::max(1, fit);
+  const double share = (double)p.workgroups / (per_cu * hw.num_cus);
+  const double resident = std::min(std::ceil((double)p.workgroups / hw.num_cus), per_cu);
+  const double per_simd = std::max(1.0, resident * nw / 4.0);
+  const double one = iters * (kIter + valu * (kAlone + kShared * (per_simd - 1.0))) + kStart + kWave * (nw - 1.0) +
+                     kExchange * (groups - 1) * ct * v.wc + kStage * ceil_div(q * ks * 4, (int)(64 * nw));
+  return kLaunch + one * std::max(1.0, 0.5 * share + 0.5 * std::ceil(share)) / kClock;
+}
+
 double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
   int nv = 0;
   const Variant* vs = all_variants(&nv);
@@ -730,6 +809,7 @@ double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc&
   if (v.gen == 5) return streaming_time_estimate(v, g, p, hw);
   if (v.gen == 6) return small_time_estimate(v, g, p, hw);
   if (v.gen == 7) return deep_time_estimate(v, g, p, hw);
+  if (v.gen == 8) return ir_time_estimate(v, g, p, hw);
   // the register kernel's structural model ranks its own plans; for comparisons with other
   // kernels the fitted figure bounds it from below
   if (v.gen == 4) return std::max(pwpw4_time_estimate(v, g, p, hw), linear_time_estimate(v, g, p));
@@ -830,6 +910,54 @@ static void collect(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, int
       }
       continue;
     }
+    if (v.gen == 8) {
+      // tiles that cut the output evenly, groups of waves, and (PW->DW) channel blocks
+      const int mc = 64 / g.elt, nch = ceil_div(g.cm, mc);
+      auto sides = [](int extent, int most) {
+        std::vector<int> s;
+        for (int i = 1; i <= extent; ++i) {
+          const int t = ceil_div(extent, i);
+          if (t <= most && (s.empty() || s.back() != t)) s.push_back(t);
+        }
+        for (int t : {4, 8, 16})
+          if (t <= most && t < extent && std::find(s.begin(), s.end(), t) == s.end()) s.push_back(t);
+        return s;
+      };
+      const std::vector<int> ths = sides(g.ho, 16), tws = sides(g.wo, 32);
+      std::vector<int> blocks = {last};
+      if (g.family == FAM_PWDW) {
+        blocks.clear();
+        for (int i = 1; i <= nch; ++i) {
+          const int bl = ceil_div(nch, i) * mc;
+          if (blocks.empty() || blocks.back() != bl) blocks.push_back(bl);
+        }
+      }
+      for (int TH : ths)
+        for (int TW : tws) {
+          // (narrow tiles fill the window copies and LDS banks badly)
+          if (TH * TW > v.max_p || TW < std::min(7, g.wo) || (TH * TW < 16 && TH < g.ho)) continue;
+          for (int bl : blocks)
+            for (int groups = 1; groups <= 8; groups *= 2) {
+              Cand c;
+              memset(&c.p, 0, sizeof(c.p));
+              c.p.op = g.op;
+              c.p.tile_h = TH;
+              c.p.tile_w = TW;
+              c.p.c_block = mc;
+              c.p.co_block = g.family == FAM_PWDW ? bl : round_up(last, 16);
+              c.p.variant = vi;
+              c.p.splits = groups;
+              if (evaluate_plan(g, d, hw, &c.p) != FCM_OK) continue;
+              c.bytes = c.p.bytes_tiled;
+              c.wgs = c.p.workgroups;
+              c.lds = c.p.lds_bytes;
+              c.area = TH * TW;
+              c.cap = v.max_cob * 1024 + v.ks;
+              cands.push_back(c);
+            }
+        }
+      continue;
+    }
     std::vector<int> cbs;
     if (v.family == FAM_DW) {
       cbs = {0};  // CB follows COB
@@ -923,15 +1051,15 @@ static fcm_status search(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
       return FCM_OK;
     }
   }
-  // The persistent (gen 3), streaming (gen 5) and whole-module (gen 6) kernels are
-  // preferred wherever one implements the shape; among them the plan with the least
-  // estimated time under its kernel family's fitted model wins.
+  // The persistent (gen 3), streaming (gen 5), whole-module (gen 6), deep (gen 7) and
+  // PW->DW(->PW) (gen 8) kernels are preferred wherever one implements the shape; among
+  // them the plan with the least estimated time under its kernel family's fitted model wins.
   {
     const Cand* best35 = nullptr;
     double best_t = 0;
     for (const Cand& c : cands) {
       const int gen = vs[c.p.variant].gen;
-      if (gen != 3 && gen != 5 && gen != 6 && gen != 7) continue;
+      if (gen != 3 && gen != 5 && gen != 6 && gen != 7 && gen != 8) continue;
       const double t = plan_time_estimate(g, c.p, hw);
       if (!best35 || t < best_t || (t == best_t && c.p.variant < best35->p.variant)) {
         best35 = &c;

@@ -1,0 +1,10 @@
+#define FCM_DT TI8
+#define FCM_DT_NAME "i8"
+#define FCM_K 3
+#define FCM_KNAME "3"
+#define FCM_TABLE_FN variants_v8_i8_k3
+#define FCM_V8_TABLE \
+  FCM_V8(1, 0, 1), FCM_V8(1, 2, 1), FCM_V8(1, 4, 1), FCM_V8(1, 6, 1), FCM_V8(1, 10, 1), FCM_V8(3, 0, \
+  1), FCM_V8(3, 2, 1), FCM_V8(3, 4, 1), FCM_V8(3, 6, 1), FCM_V8(3, 10, 1), FCM_V8(1, 0, 2), FCM_V8(1, \
+  2, 2), FCM_V8(1, 4, 2)
+#include "k_v8.inc"
