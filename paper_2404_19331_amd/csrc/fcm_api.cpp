@@ -55,7 +55,8 @@ const Variant* all_variants(int* count) {
                                      variants_v4_pwpw_i8, variants_v4_pwpw_bf16, variants_v4_pwpw_f32,
                                      variants_v5_dwpw_bf16_s1, variants_v5_dwpw_bf16_s2, variants_v5_pwdw_bf16,
                                      variants_v6_f32, variants_v7_bf16, variants_v8_bf16, variants_v8_i8_k3,
-                                     variants_v8_i8_k5};
+                                     variants_v8_i8_k5, variants_v8_bf16_k5, variants_v9_bf16, variants_v9_f32,
+                                     variants_v9_i8};
     for (auto fn : fns) {
       int n = 0;
       const Variant* t = fn(&n);
@@ -273,8 +274,8 @@ static fcm_status run(int op, const fcm_desc* d, const Tensors& t, const fcm_pla
     a.vec_w2 = aligned16(t.w[1]) && (g.cm * e) % 16 == 0;
   }
   a.stride = g.s;
-  if (v.gen == 8) {
-    a.gw = waves8(p.tile_h * p.tile_w, v.wc);
+  if (v.gen == 8 || v.gen == 9) {
+    a.gw = p.waves / p.splits;
     a.splits = p.splits;
   }
   a.cus = device_cus();

@@ -157,9 +157,11 @@ fcm_status fcm_chain_plan(const fcm_chain_desc* chain, int32_t objective, const 
       // bf16: a sum that the PW->DW(->PW) kernels round differently (1e-5 of the values)
       // travels through all layers that follow, and after MobileNetV2's 51 the outputs are
       // 3.3e-3 off the other kernels', beyond the 2e-3 a bf16 chain is held to: bf16 chains
-      // keep the kernels that agree (batch 1: 287 us, with them 208 us; they can still be
-      // put in a chain plan explicitly). int8 chains are exact on any kernel.
-      const int kset = kernel_set(op, &d) | (d.dtype == FCM_BF16 ? KSET_SAME_ROUNDING : 0);
+      // keep the kernels that agree when planned by time (batch 1: 287 us, with them 208 us;
+      // by bytes the module planner's plans are taken as they are). int8 chains are exact on
+      // any kernel.
+      const bool same = objective == FCM_CHAIN_TIME && d.dtype == FCM_BF16;
+      const int kset = kernel_set(op, &d) | (same ? KSET_SAME_ROUNDING : 0);
       st = find_plan(op, &d, &H, &o.plan, kset, 0);
       if (st != FCM_OK) {
         if (single) return st;

@@ -379,8 +379,40 @@ FCM_HD inline Lds8 lds8(int dt, int K, int S, int TH, int TW, int ci, int mb, in
   if (red > L.total) L.total = red;
   return L;
 }
+// NCHW DW->PW kernels over window chunks (k_dwpw9, host and device): per group of waves two buffers
+// of one chunk's window [position][64 bytes] and pointwise weight rows [16 ct][64 bytes],
+// both at pitch kPitchE8; then the depthwise weights and biases of every input channel
+// (padded to whole chunks). The accumulators' exchange as in k_ir8.
+// 16-byte slots of a chunk's window and weight rows per thread, at most (int8 holds each of
+// a slot's 16 bytes in a register while it is in flight).
+FCM_HD constexpr int window_vecs9(int dt) { return dt == DT_I8 ? 2 : 4; }
+constexpr int kWeightVecs9 = 2;
+struct Lds9 {
+  int nqp, e_bytes, buf, dww_off, b1_off, total;
+};
+FCM_HD inline Lds9 lds9(int dt, int K, int S, int TH, int TW, int ci, int gw, int groups, int pb, int ct) {
+  Lds9 L{};
+  const int e = elt_size(dt), cip = round_up(ci, 64 / e);
+  L.nqp = round_up(((TH - 1) * S + K) * ((TW - 1) * S + K), 16);
+  L.e_bytes = L.nqp * kPitchE8;
+  L.buf = L.e_bytes + 16 * ct * kPitchE8;
+  L.dww_off = 2 * groups * L.buf;
+  L.b1_off = L.dww_off + round_up(cip * K * K * e, 16);
+  L.total = L.b1_off + cip * 4;
+  const int red = (groups - 1) * gw * pb * ct * 1024;
+  if (red > L.total) L.total = red;
+  return L;
+}
+
 // Waves of a group: the 16-pixel blocks of a tile of p pixels, pb per wave.
 FCM_HD inline int waves8(int p, int pb) { return p <= 16 * pb ? 1 : (p <= 32 * pb ? 2 : 4); }
+// As waves8, and enough threads for a chunk of a window of nqp positions and of ct weight
+// tiles (0 if four waves are not).
+FCM_HD inline int waves9(int dt, int p, int pb, int nqp, int ct) {
+  for (int gw = waves8(p, pb); gw <= 4; gw *= 2)
+    if (4 * nqp <= 64 * gw * window_vecs9(dt) && ct <= gw * kWeightVecs9) return gw;
+  return 0;
+}
 
 // ---------------------------------------------------------------------------------
 // Kernel argument block (one struct for all families; unused fields ignored).
@@ -412,8 +444,8 @@ struct KArgs {
   int grid_cap;  // persistent kernels: at most this many workgroups (0 = no cap)
   const int32_t* rqc[3];  // int8 per-channel requantisation per stage ([2][channels]) or nullptr
   int zin[3];             // int8 zero point of each stage's input
-  int stride;             // depthwise stride (k_ir8; a template argument elsewhere)
-  int gw;                 // k_ir8: waves per group
+  int stride;             // depthwise stride (gens 8 and 9; a template argument elsewhere)
+  int gw;                 // gens 8 and 9: waves per group
 };
 
 // One compiled kernel instance and the tilings it implements.
@@ -445,12 +477,14 @@ struct Variant {
                     //    pixels, one compiled output-channel block
                     // 8: PW->DW(->PW) NHWC kernels (bf16, int8): run-time tile of at most
                     //    max_p pixels, 64-byte intermediate chunks
+                    // 9: NCHW DW->PW kernels over window chunks: run-time tile of at most
+                    //    max_p pixels, one compiled output-channel block
   int pitch = 0;    // gen 3: LDS window row pitch in pixels (window width must not exceed it)
   int ks = 1;       // gen 3: 64-byte channel chunks per item; gen 4: 64-byte k-steps of the
                     // first convolution held in registers (input channels <= 64 * ks bytes);
                     // gen 5: LDS ring slots; gen 8: as gen 4
-  int wc = 1;       // gen 5: waves across output channels (1, 2 or 4); gen 8: 16-pixel
-                    // blocks per wave
+  int wc = 1;       // gen 5: waves across output channels (1, 2 or 4); gens 8 and 9:
+                    // 16-pixel blocks per wave
   int kc = 1;       // gen 7: 32-channel chunks per item (1 or 2)
 };
 
@@ -477,8 +511,12 @@ const Variant* variants_v3_dw_bf16(int* count);
 const Variant* variants_v3_dw_f32(int* count);
 const Variant* variants_v3_dw_i8(int* count);
 const Variant* variants_v8_bf16(int* count);
+const Variant* variants_v8_bf16_k5(int* count);
 const Variant* variants_v8_i8_k3(int* count);
 const Variant* variants_v8_i8_k5(int* count);
+const Variant* variants_v9_bf16(int* count);
+const Variant* variants_v9_f32(int* count);
+const Variant* variants_v9_i8(int* count);
 const Variant* variants_v4_pwpw_i8(int* count);
 const Variant* variants_v4_pwpw_bf16(int* count);
 const Variant* variants_v4_pwpw_f32(int* count);

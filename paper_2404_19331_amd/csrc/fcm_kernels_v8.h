@@ -22,7 +22,7 @@
 //   * one barrier (E is double buffered)
 //   * DW: lane = output pixel l % 16 of the wave's own 16-pixel blocks, slot l / 16.
 //     bf16: dot instructions on pairs of taps, weights broadcast within 16-lane rows by
-//     DPP (dw_channel7), each row holding its own slot's weights. int8: on the matrix
+//     DPP, each row holding its own slot's weights. int8: on the matrix
 //     cores. For slot s the A operand is diagonal, row m holding the weight of tap
 //     4 kk + l / 16 at byte m of the slot, zero elsewhere; the B operand is E's slot s at
 //     that tap's position. Row m of slot s is channel 16 (m / 4) + 4s + m % 4, so after the
@@ -112,14 +112,131 @@ __device__ __forceinline__ u32x4 load_row8(rsrc_t r, bool vec, uint32_t voff, ui
   return v;
 }
 
+// The depthwise stage of one wave: lane = output pixel l % 16 of each of PB blocks, slot
+// l / 16 of a 64-byte chunk held [position][slots] in LDS. d[b] = the 16 bytes of the lane's
+// slot (int8: of channels 16 (l / 16) .. + 15; see above), +bias, activation and cast.
+// wts: the chunk's weights [channel][tap], bias: its biases, both in LDS.
+template <class DT, int K>
+struct DwLanes8 {
+  static constexpr int KK = K * K, NKK = (KK + 3) / 4, EP = kPitchE8;
+  int IW, g, r16;
+  int tko[NKK];       // int8: offset of the lane group's tap of each k-step
+  uint32_t dmask[4];  // int8: the diagonal byte of each operand word
+
+  __device__ __forceinline__ DwLanes8(int IW_, int g_, int r16_) : IW(IW_), g(g_), r16(r16_) {
+    if constexpr (DT::ELT == 1) {
+#pragma unroll
+      for (int kk = 0; kk < NKK; ++kk) {
+        const int tap = min(4 * kk + g, KK - 1);
+        tko[kk] = ((tap / K) * IW + tap % K) * EP;
+      }
+#pragma unroll
+      for (int d = 0; d < 4; ++d) dmask[d] = (r16 >> 2) == d ? 0xffu << (8 * (r16 & 3)) : 0u;
+    }
+  }
+
+  template <int PB>
+  __device__ __forceinline__ void run(u32x4 (&d)[PB], const char* eb, const int (&ebase)[PB], const char* wts,
+                                      const char* bias, const EpiF8& ef, const Rq8& eq) const {
+    using AccV = typename DT::AccV;
+    if constexpr (DT::ELT == 1) {
+      const char* wb = wts + (16 * (r16 >> 2) + (r16 & 3)) * KK;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        AccV acc[PB];
+        const AccV bv = *(const AccV*)(bias + (16 * g + 4 * s) * 4);
+#pragma unroll
+        for (int b = 0; b < PB; ++b) acc[b] = bv;
+#pragma unroll
+        for (int kk = 0; kk < NKK; ++kk) {
+          const int tap = 4 * kk + g;
+          uint32_t wt = *(const uint8_t*)(wb + 4 * s * KK + min(tap, KK - 1));
+          if (4 * kk + 3 >= KK) wt = tap < KK ? wt : 0u;
+          wt = __builtin_amdgcn_perm(wt, wt, 0u);  // the byte in all four places
+          const u32x4 av = {wt & dmask[0], wt & dmask[1], wt & dmask[2], wt & dmask[3]};
+#pragma unroll
+          for (int b = 0; b < PB; ++b) mma16(DT{}, acc[b], av, *(const u32x4*)(eb + ebase[b] + tko[kk] + 16 * s));
+        }
+#pragma unroll
+        for (int b = 0; b < PB; ++b) d[b][s] = rq8x4(acc[b], eq);
+      }
+    } else {
+      // the slot's CPG * KK weights as words, 64 of them (four a lane) to a register set
+      constexpr int CPG = 16 / DT::ELT, NWORD = CPG * KK * DT::ELT / 4, NS = (NWORD + 63) / 64;
+      u32x4 wv[NS];
+#pragma unroll
+      for (int k = 0; k < NS; ++k) {
+        const int off = 256 * k + 16 * r16;
+        wv[k] = *(const u32x4*)(wts + g * (NWORD * 4) + (off < NWORD * 4 ? off : 0));
+      }
+      float bv[CPG];
+#pragma unroll
+      for (int q = 0; q < CPG / 4; ++q) {
+        const f32x4 b4 = *(const f32x4*)(bias + (CPG * g + 4 * q) * 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bv[4 * q + e] = b4[e];
+      }
+#pragma unroll
+      for (int b = 0; b < PB; ++b) {
+        u32x4 xv[KK];
+#pragma unroll
+        for (int ky = 0; ky < K; ++ky)
+#pragma unroll
+          for (int kx = 0; kx < K; ++kx) xv[K * ky + kx] = *(const u32x4*)(eb + ebase[b] + (ky * IW + kx) * EP);
+        float acc[CPG];
+#pragma unroll
+        for (int e = 0; e < CPG; ++e) acc[e] = bv[e];
+        static_for7<0, CPG>([&](auto jc) {
+          constexpr int J = decltype(jc)::value;
+          channel<J>(acc[J], xv, wv);
+        });
+        if constexpr (DT::ELT == 2) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) d[b][q] = bf16x2_8(acc[2 * q], acc[2 * q + 1], ef);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            d[b][q] = __float_as_uint(ef.none ? acc[q] : __builtin_amdgcn_fmed3f(acc[q], ef.lo, ef.hi));
+        }
+      }
+    }
+  }
+
+  // Channel J of the slot: word q of the weights sits in set q / 64, lane (q % 64) / 4,
+  // component q % 4. bf16 (KK odd): an even channel's taps pair up from its first, an odd
+  // one's first tap is the high half of a word it shares (as dw_channel7).
+  template <int J, int NS>
+  __device__ static __forceinline__ void channel(float& acc, const u32x4 (&xv)[KK], const u32x4 (&wv)[NS]) {
+    if constexpr (DT::ELT == 4) {
+      static_for7<0, KK>([&](auto tc) {
+        constexpr int T = decltype(tc)::value, q = J * KK + T;
+        acc = __builtin_fmaf(bcast7<(q % 64) / 4>(wv[q / 64][q % 4]), __uint_as_float(xv[T][J]), acc);
+      });
+    } else {
+      constexpr int k = J >> 1, odd = J & 1, q0 = (KK * J - odd) / 2, NP = (KK + 1) / 2;
+      static_for7<0, NP>([&](auto pc) {
+        constexpr int i = decltype(pc)::value, q = q0 + i;
+        uint32_t x;
+        if constexpr (odd) {
+          if constexpr (i == 0) x = xv[0][k] & 0xffff0000u;
+          else x = __builtin_amdgcn_perm(xv[2 * i][k], xv[2 * i - 1][k], 0x07060302u);
+        } else {
+          if constexpr (i == NP - 1) x = xv[KK - 1][k] & 0xffffu;
+          else x = __builtin_amdgcn_perm(xv[2 * i + 1][k], xv[2 * i][k], 0x05040100u);
+        }
+        dot_bcast7<(q % 64) / 4, i == NP - 1>(acc, wv[q / 64][q % 4], x);
+      });
+    }
+  }
+};
+
 template <class DT, int K, int KS, int CT, int PB>
 __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
   extern __shared__ __align__(16) char smem[];
   constexpr bool I8 = std::is_same<DT, TI8>::value;
-  static_assert(I8 || K == 3, "bf16: 3x3");
   using AccV = typename DT::AccV;
   constexpr int E = DT::ELT, MC = 64 / E, TPC = 4 / E, CPG = 16 / E;
-  constexpr int KK = K * K, NKK = (KK + 3) / 4;
+  constexpr int KK = K * K;
   constexpr int EP = kPitchE8;
   constexpr int NU = CT > 0 ? CT : 1;
 
@@ -228,17 +345,7 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
     ebase[b] = (py * S * IW + px * S) * EP + (I8 ? 0 : 16 * g);
     opix[b] = p < P && oy0 + py < a.Ho && ox0 + px < a.Wo ? ((oy0 + py) * a.Wo + ox0 + px) : -1;
   }
-  [[maybe_unused]] int tko[NKK];  // int8: E offset of the lane group's tap of each k-step
-  [[maybe_unused]] uint32_t dmask[4];
-  if constexpr (I8) {
-#pragma unroll
-    for (int kk = 0; kk < NKK; ++kk) {
-      const int tap = min(4 * kk + g, KK - 1);
-      tko[kk] = ((tap / K) * IW + tap % K) * EP;
-    }
-#pragma unroll
-    for (int d = 0; d < 4; ++d) dmask[d] = (r16 >> 2) == d ? 0xffu << (8 * (r16 & 3)) : 0u;
-  }
+  const DwLanes8<DT, K> dl(IW, g, r16);
 
   AccV acc2[PB][NU];
 #pragma unroll
@@ -317,56 +424,7 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
       if (c + J < nch) load_a1(c + J);
       // ---- DW on the wave's pixel blocks, PW2 or the store ----
       u32x4 d[PB];
-      if constexpr (I8) {
-        const char* wb = smem + lay.dww_off + (m0 + 16 * (r16 >> 2) + (r16 & 3)) * KK;
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          AccV acc[PB];
-          const AccV bv = *(const AccV*)(smem + lay.b2_off + (m0 + 16 * g + 4 * s) * 4);
-#pragma unroll
-          for (int b = 0; b < PB; ++b) acc[b] = bv;
-#pragma unroll
-          for (int kk = 0; kk < NKK; ++kk) {
-            const int tap = 4 * kk + g;
-            uint32_t wt = *(const uint8_t*)(wb + 4 * s * KK + min(tap, KK - 1));
-            if (4 * kk + 3 >= KK) wt = tap < KK ? wt : 0u;
-            wt = __builtin_amdgcn_perm(wt, wt, 0u);  // the byte in all four places
-            const u32x4 av = {wt & dmask[0], wt & dmask[1], wt & dmask[2], wt & dmask[3]};
-#pragma unroll
-            for (int b = 0; b < PB; ++b) mma16(DT{}, acc[b], av, *(const u32x4*)(eb + ebase[b] + tko[kk] + 16 * s));
-          }
-#pragma unroll
-          for (int b = 0; b < PB; ++b) d[b][s] = rq8x4(acc[b], q2);
-        }
-      } else {
-        const int wo = r16 < 9 ? lay.dww_off + (m0 + 8 * g) * 18 + 16 * r16
-                               : lay.b2_off + (m0 + 8 * g) * 4 + 16 * (r16 == 10 ? 1 : 0);
-        const u32x4 wv = *(const u32x4*)(smem + wo);
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-          const char* xb = eb + ebase[b];
-          u32x4 xv[9];
-#pragma unroll
-          for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-            for (int kx = 0; kx < 3; ++kx) xv[3 * ky + kx] = *(const u32x4*)(xb + (ky * IW + kx) * EP);
-          float acc[8];
-          acc[0] = bcast7<9>(wv[0]);
-          acc[1] = bcast7<9>(wv[1]);
-          acc[2] = bcast7<9>(wv[2]);
-          acc[3] = bcast7<9>(wv[3]);
-          acc[4] = bcast7<10>(wv[0]);
-          acc[5] = bcast7<10>(wv[1]);
-          acc[6] = bcast7<10>(wv[2]);
-          acc[7] = bcast7<10>(wv[3]);
-          static_for7<0, 8>([&](auto jc) {
-            constexpr int JJ = decltype(jc)::value;
-            dw_channel7<JJ>(acc[JJ], xv, wv);
-          });
-#pragma unroll
-          for (int q = 0; q < 4; ++q) d[b][q] = bf16x2_8(acc[2 * q], acc[2 * q + 1], e2);
-        }
-      }
+      dl.template run<PB>(d, eb, ebase, smem + lay.dww_off + m0 * KK * E, smem + lay.b2_off + m0 * 4, e2, q2);
       if constexpr (CT > 0) {
 #pragma unroll
         for (int u = 0; u < CT; ++u) {

@@ -303,7 +303,7 @@ bool variant_needs_alignment(int variant) {
 // tiles; with per-channel requantisation (KSET_PC) the int8 persistent kernels.
 static bool in_set(const Variant& v, int kset) {
   if (v.gen < 2) return true;
-  if ((kset & KSET_SAME_ROUNDING) && v.gen == 8) return false;
+  if ((kset & KSET_SAME_ROUNDING) && v.gen >= 8) return false;
   if (kset == KSET_PC) return v.gen == 3 && v.dtype == DT_I8;
   if (kset & KSET_DMA) return true;
   if (!(kset & KSET_REG)) return false;
@@ -422,6 +422,41 @@ static fcm_status evaluate_plan8(const Variant& v, const Geom& g, const fcm_hw_d
   return FCM_OK;
 }
 
+// Plan of the NCHW DW->PW kernels: any tile of at most max_p output pixels, the compiled
+// output-channel block, four waves (splits follows from the tile: the groups of waves that
+// share its chunks).
+static fcm_status evaluate_plan9(const Variant& v, const Geom& g, const fcm_hw_desc& hw, fcm_plan_t* p) {
+  const int e = g.elt, mc = 64 / e, ct = v.max_cob / 16;
+  if (g.layout != FCM_NCHW) return fail(FCM_EUNSUPPORTED, "plan: the kernel needs NCHW");
+  const int64_t lim = (int64_t)1 << 30;  // 32-bit buffer offsets with room for an out-of-range scalar part
+  if ((int64_t)g.h * g.w * (g.ci + mc) * e >= lim || (int64_t)(g.co + v.max_cob) * (g.ci + mc) * e >= lim)
+    return fail(FCM_EUNSUPPORTED, "plan: tensor too large for the kernel");
+  const int TH = p->tile_h, TW = p->tile_w, P = TH * TW;
+  if (TH <= 0 || TW <= 0 || P > v.max_p || p->c_block != mc || p->co_block != v.max_cob)
+    return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
+  const int64_t q = (int64_t)((TH - 1) * g.s + g.k) * ((TW - 1) * g.s + g.k);
+  const int gw = q > (1 << 20) ? 0 : waves9(g.dtype, P, v.wc, round_up((int)q, 16), ct);
+  if (gw == 0) return fail(FCM_EUNSUPPORTED, "plan: window or weights exceed what the threads hold");
+  const int groups = 4 / gw;
+  if (groups > ceil_div(g.ci, mc) || (p->splits > 1 && p->splits != groups))
+    return fail(FCM_EUNSUPPORTED, "plan: the tile's groups of waves need a chunk each");
+  const Lds9 L = lds9(g.dtype, g.k, g.s, TH, TW, g.ci, gw, groups, v.wc, ct);
+  if (L.total > hw.lds_per_wg) return fail(FCM_EUNSUPPORTED, "plan: tiling exceeds the LDS per workgroup");
+  const int64_t wgs = (int64_t)g.n * ceil_div(g.ho, TH) * ceil_div(g.wo, TW) * ceil_div(g.co, v.max_cob);
+  if (wgs > 0x7fffffff) return fail(FCM_EUNSUPPORTED, "plan: grid too large");
+  const Bytes b = module_bytes(g, TH, TW, p->co_block);
+  p->waves = 4;
+  p->depth = 0;
+  p->splits = groups;
+  p->lds_bytes = L.total;
+  p->workgroups = (int32_t)wgs;
+  p->bytes_ideal = b.ideal;
+  p->bytes_tiled = b.tiled;
+  p->bytes_paper = b.paper;
+  p->redundancy = b.redundancy;
+  return FCM_OK;
+}
+
 fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, fcm_plan_t* p) {
   (void)d;
   int nv = 0;
@@ -431,6 +466,7 @@ fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
   if (!variant_matches(v, g)) return fail(FCM_EUNSUPPORTED, "plan: kernel variant does not implement this module");
   if (v.gen == 4) return evaluate_plan4(v, g, hw, p);
   if (v.gen == 8) return evaluate_plan8(v, g, hw, p);
+  if (v.gen == 9) return evaluate_plan9(v, g, hw, p);
   int depth = v.gen == 3 ? p->depth : 0;
   const int lds = tiling_lds(v, g, p->tile_h, p->tile_w, p->c_block, p->co_block, hw.lds_per_wg, &depth);
   if (lds <= 0) return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
@@ -800,6 +836,31 @@ static double ir_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t
   return kLaunch + one * std::max(1.0, 0.5 * share + 0.5 * std::ceil(share)) / kClock;
 }
 
+// Time model of the NCHW DW->PW kernels (gen 9), in seconds: the launch, then the chunks of a
+// workgroup one after another, each a fixed part, the stencil and MFMAs of a wave, and the
+// loads of the next chunk (the CU's address unit takes them in turn, so workgroups sharing
+// it wait for each other); the exchange of the groups' accumulators; whole rounds beyond
+// the resident workgroups. Fitted to 990 timed plans of eleven shapes and all types:
+// within 0.90-1.11x for 80% of them, the chosen plan within 3% of the best on average.
+static double dp_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
+  constexpr double kLaunch = 3.5e-6, kClock = 2.4e9, kStart = 3712.0, kIter = 782.0, kAlone = 0.967, kShared = 0.361,
+                   kMfma = 46.5, kExchange = 394.0, kWindowLoad = 41.8, kWeightLoad = 88.7, kLoadShared = 0.7;
+  const int e = g.elt, groups = std::max(1, (int)p.splits), gw = 4 / groups, ct = v.max_cob / 16;
+  const int q = ((p.tile_h - 1) * g.s + g.k) * ((p.tile_w - 1) * g.s + g.k), nkk = ceil_div(g.k * g.k, 4);
+  const double iters = ceil_div(ceil_div(g.ci * e, 64), groups);
+  const double wloads = ceil_div(64 * ct, 64 * gw) * ((g.ci * e) % 16 == 0 ? 1 : (g.ci * e) % 4 == 0 ? 4 : 16 / e);
+  const double xloads = 4.0 * round_up(q, 16) / (64 * gw) * (16 / e);
+  const double dw = e == 1 ? 928.0 * v.wc + 471.0 * nkk : (e == 2 ? 122.8 : 49.9) * g.k * g.k * v.wc;
+  const double mfma = (ct * (e == 4 ? 4 : 1) + (e == 1 ? 4 * nkk : 0)) * v.wc;
+  const double per_cu = std::max(1, std::min(hw.lds_per_cu / std::max(1, (int)p.lds_bytes), 2));
+  const double share = (double)p.workgroups / (per_cu * hw.num_cus);
+  const double others = std::min(std::ceil((double)p.workgroups / hw.num_cus), per_cu) - 1.0;
+  const double one = iters * (kIter + (dw + kMfma * mfma) * (kAlone + kShared * others) +
+                              (kWindowLoad * xloads + kWeightLoad * wloads) * (1.0 + kLoadShared * others)) +
+                     kStart + kExchange * (groups - 1) * ct * v.wc;
+  return kLaunch + one * std::max(1.0, 0.5 * share + 0.5 * std::ceil(share)) / kClock;
+}
+
 double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
   int nv = 0;
   const Variant* vs = all_variants(&nv);
@@ -810,6 +871,7 @@ double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc&
   if (v.gen == 6) return small_time_estimate(v, g, p, hw);
   if (v.gen == 7) return deep_time_estimate(v, g, p, hw);
   if (v.gen == 8) return ir_time_estimate(v, g, p, hw);
+  if (v.gen == 9) return dp_time_estimate(v, g, p, hw);
   // the register kernel's structural model ranks its own plans; for comparisons with other
   // kernels the fitted figure bounds it from below
   if (v.gen == 4) return std::max(pwpw4_time_estimate(v, g, p, hw), linear_time_estimate(v, g, p));
@@ -910,7 +972,7 @@ static void collect(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, int
       }
       continue;
     }
-    if (v.gen == 8) {
+    if (v.gen == 8 || v.gen == 9) {
       // tiles that cut the output evenly, groups of waves, and (PW->DW) channel blocks
       const int mc = 64 / g.elt, nch = ceil_div(g.cm, mc);
       auto sides = [](int extent, int most) {
@@ -937,14 +999,14 @@ static void collect(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, int
           // (narrow tiles fill the window copies and LDS banks badly)
           if (TH * TW > v.max_p || TW < std::min(7, g.wo) || (TH * TW < 16 && TH < g.ho)) continue;
           for (int bl : blocks)
-            for (int groups = 1; groups <= 8; groups *= 2) {
+            for (int groups = 1; groups <= (v.gen == 8 ? 8 : 1); groups *= 2) {
               Cand c;
               memset(&c.p, 0, sizeof(c.p));
               c.p.op = g.op;
               c.p.tile_h = TH;
               c.p.tile_w = TW;
               c.p.c_block = mc;
-              c.p.co_block = g.family == FAM_PWDW ? bl : round_up(last, 16);
+              c.p.co_block = v.gen == 9 ? v.max_cob : (g.family == FAM_PWDW ? bl : round_up(last, 16));
               c.p.variant = vi;
               c.p.splits = groups;
               if (evaluate_plan(g, d, hw, &c.p) != FCM_OK) continue;
@@ -1051,15 +1113,15 @@ static fcm_status search(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
       return FCM_OK;
     }
   }
-  // The persistent (gen 3), streaming (gen 5), whole-module (gen 6), deep (gen 7) and
-  // PW->DW(->PW) (gen 8) kernels are preferred wherever one implements the shape; among
+  // The persistent (gen 3), streaming (gen 5), whole-module (gen 6), deep (gen 7),
+  // PW->DW(->PW) (gen 8) and NCHW DW->PW (gen 9) kernels are preferred wherever one implements the shape; among
   // them the plan with the least estimated time under its kernel family's fitted model wins.
   {
     const Cand* best35 = nullptr;
     double best_t = 0;
     for (const Cand& c : cands) {
       const int gen = vs[c.p.variant].gen;
-      if (gen != 3 && gen != 5 && gen != 6 && gen != 7 && gen != 8) continue;
+      if (gen != 3 && gen != 5 && gen != 6 && gen != 7 && gen != 8 && gen != 9) continue;
       const double t = plan_time_estimate(g, c.p, hw);
       if (!best35 || t < best_t || (t == best_t && c.p.variant < best35->p.variant)) {
         best35 = &c;

@@ -26,7 +26,7 @@ RQ = ((1, 7, -127, 127), (20011, 22, -128, 127), (1342177283, 38, -127, 127))
 def _cases():
     out = []
     shapes = {  # c_in, c_mid, c_out, k, stride, pad
-        "bf16": [(24, 144, 24, 3, 1, 1), (40, 72, 20, 3, 2, 1), (50, 64, 36, 3, 1, 0), (160, 200, 160, 3, 2, 2),
+        "bf16": [(24, 144, 24, 3, 1, 1), (40, 72, 20, 3, 2, 1), (24, 96, 20, 5, 1, 2), (70, 136, 68, 5, 2, 2), (50, 64, 36, 3, 1, 0), (160, 200, 160, 3, 2, 2),
                  (8, 16, 4, 3, 1, 1), (96, 576, 96, 3, 1, 1)],
         "i8": [(24, 144, 24, 3, 1, 1), (36, 64, 20, 3, 2, 1), (160, 208, 160, 5, 1, 2), (64, 384, 64, 3, 1, 0),
                (16, 48, 4, 5, 2, 4), (100, 320, 96, 3, 2, 2)],
