@@ -156,6 +156,19 @@ struct Dw3<TI8> {
   }
 };
 
+// 4x4 transpose of dwords over the four 16-lane rows of a wave: row g's word s becomes row
+// s's word g.
+__device__ __forceinline__ void transpose_rows4(u32x4& v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const uint32_t v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+  const u2 a = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(v0, v2, false, false));
+  const u2 b = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(v1, v3, false, false));
+  const uint32_t a0 = a[0], a1 = a[1], b0 = b[0], b1 = b[1];
+  const u2 c = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a0, b0, false, false));
+  const u2 e = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a1, b1, false, false));
+  v = u32x4{c[0], c[1], e[0], e[1]};
+}
+
 // s_waitcnt vmcnt(n) with the other counters left alone, for a run-time n in [0, 63]:
 // gfx9 encoding vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14.
 template <int N>
@@ -206,7 +219,14 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
   static_assert(CPL * 4 == CB, "lane slot layout");
   static_assert(IWP % 16 == 0, "window pitch");
   static_assert(MODE != M3_DW || KS == 1, "a depthwise-only item is one chunk");
-  static_assert(QX == 0 || std::is_same<DT, TI8>::value, "zero points / per-channel: int8");
+  constexpr bool I8 = std::is_same<DT, TI8>::value;
+  static_assert(QX == 0 || I8, "zero points / per-channel: int8");
+  // int8 5x5: the stencil on the matrix cores (112x112x96 -> 24 stride 2: 12.9 -> 12.3 us;
+  // 14x14x480 -> 112 with zero points and per-channel scales 18.4 -> 17.4 us). 3x3 keeps the
+  // dot instructions: its few taps do not pay for the weight operands and the operand's LDS
+  // reads, which meet in a quarter of the banks (the MobileNetV2 body 362 against 335 us;
+  // swizzling the slots cost more in address arithmetic than it gained).
+  constexpr bool MXDW = I8 && HAS_DW && KK > 9;
   constexpr int PCQ = QX == 2 ? 1 : 0;  // per-channel multipliers and shifts staged
   // Output-channel order of the PW accumulators: lane (l % 16, g = l / 16) of tile i holds
   // values v = 0..3 of channel OGE * (4 * (i / OTPG) + g) + 4 * (i % OTPG) + v, so that the
@@ -432,7 +452,7 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
     // Depthwise weights of the item in ring slot `slot` (wave 0): raw [c][tap] elements
     // -> [tap][c] dot-operand words. All reads are issued before the first write.
     auto convert = [&](int slot) {
-      if constexpr (HAS_DW) {
+      if constexpr (HAS_DW && !MXDW) {  // (the matrix cores' operands take them raw)
         if (wave != 0) return;
         constexpr int NEL = CB * KK;                      // weights of the chunk
         constexpr int EPV = 16 / DT::ELT;                 // elements per 16-byte vector
@@ -511,6 +531,21 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
   const int a_row = r16 * kRowB + ((g ^ (((r16 >> 3) & 1) << 1)) * 16);  // swizzled MFMA A slot
   const Epi3 ep_dw = make_epi3(a.act[0], a.rq[0]);
   const Epi3 ep_pw = MODE == M3_PW ? ep_dw : make_epi3(a.act[1], a.rq[1]);
+  [[maybe_unused]] const Rq8 rq_dw = make_rq8(a.rq[0], a.act[0]);
+  // MXDW: window offset of this lane group's tap of each k-step (four taps), and the
+  // diagonal byte of each word of the weight operand
+  constexpr int NKK = (KK + 3) / 4;
+  [[maybe_unused]] int tko[NKK];
+  [[maybe_unused]] uint32_t dmask[4];
+  if constexpr (MXDW) {
+#pragma unroll
+    for (int kk = 0; kk < NKK; ++kk) {
+      const int tap = min(4 * kk + g, KK - 1), ky = tap / KE, kx = tap - ky * KE;
+      tko[kk] = (ky * IWP + (SE == 2 ? (kx & 1) * (IWP / 2) + (kx >> 1) : kx)) * kRowB - g * 16;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) dmask[q] = (r16 >> 2) == q ? 0xffu << (8 * (r16 & 3)) : 0u;
+  }
   // Asymmetric int8 PW input (zero point z_pw): every output channel loses z_pw x its
   // weight-row sum, which each lane accumulates from its A operands (16 bytes of a row per
   // chunk) and completes at the epilogue.
@@ -544,7 +579,59 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
 #pragma unroll
       for (int s = 0; s < KS; ++s) {  // the item's channel chunks, one plane each
         const char* plane = buf + s * lay.plane_bytes;
-        if constexpr (HAS_DW) {
+        if constexpr (MXDW) {
+          // 16 channels (slot q of the chunk) of 16 pixels per MFMA chain: B = the slot at
+          // four taps (one per lane group), A = the taps' weights on the diagonal (row m:
+          // byte m), so the accumulators hold channels 16q + 4g + [0, 4) of pixel l % 16.
+          // A dot instruction per tap and channel uses one of its four products; here 28
+          // MFMAs a block take the place of 400 dots, the operand's five instructions
+          // shared by the wave's blocks.
+          const char* raw = plane + lay.raw_off + r16 * KK;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            AccV dacc[NB];
+            const AccV bv = *(const AccV*)(buf + lay.bias_off + (s * CB + 16 * q + 4 * g) * 4);
+#pragma unroll
+            for (int b = 0; b < NB; ++b) dacc[b] = bv;
+#pragma unroll
+            for (int kk = 0; kk < NKK; ++kk) {
+              const int tap = 4 * kk + g;
+              uint32_t wt = *(const uint8_t*)(raw + 16 * q * KK + min(tap, KK - 1));
+              if (4 * kk + 3 >= KK) wt = tap < KK ? wt : 0u;
+              wt = __builtin_amdgcn_perm(wt, wt, 0u);  // the byte in all four places
+              const u32x4 av = {wt & dmask[0], wt & dmask[1], wt & dmask[2], wt & dmask[3]};
+              int t = tko[kk];
+              asm volatile("" : "+v"(t));  // (else every block's sum with it is kept over the items)
+#pragma unroll
+              for (int b = 0; b < NB; ++b) mma16(DT{}, dacc[b], av, *(const u32x4*)(plane + base[b] + t + 16 * q));
+            }
+            if (PCQ && pc_dw) {  // (uniform) the four channels' multipliers, then (512 bytes on) shifts
+              const char* pm = buf + lay.bias_off + 2048 + (s * CB + 16 * q + 4 * g) * 4;
+              const u32x4 mv = *(const u32x4*)pm, sv = *(const u32x4*)(pm + 512);
+              double sc[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) sc[e] = rq_scale((int32_t)mv[e], pc_shift(sv[e]));
+#pragma unroll
+              for (int b = 0; b < NB; ++b) {
+                uint32_t wv = 0;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                  const int32_t v = dacc[b][e];
+                  wv |= ((uint32_t)(rq_round(v, sc[e], ep_dw.range) + ep_dw.zp) & 0xffu) << (8 * e);
+                }
+                bop[b][q] = wv;
+              }
+            } else {
+#pragma unroll
+              for (int b = 0; b < NB; ++b) bop[b][q] = rq8x4(dacc[b], rq_dw);
+            }
+            // (one slot's operands live at a time: scheduled together the four spill)
+            __builtin_amdgcn_sched_barrier(0);
+          }
+          // channels 16q + 4g + v -> 16g + 4q + v: this lane's 16 consecutive channels
+#pragma unroll
+          for (int b = 0; b < NB; ++b) transpose_rows4(bop[b]);
+        } else if constexpr (HAS_DW) {
           Acc dacc[NB][CPL];
           const char* wl = plane + lay.wd_off;
           {

@@ -46,47 +46,6 @@ namespace fcm {
 
 constexpr int kMaxWaves8 = 8;
 
-// int8 requantisation of a stage: in single precision where that is exact, else in double
-// (rq_round). Single precision is exact for every int32 accumulator if the multiplier has
-// at most 24 bits (the scale is then a float and the fma's product exact) and the scale is
-// at least 2^-16: an accumulator beyond 2^24, which the conversion rounds, then lies
-// beyond the clamp. 12 SIMD cycles a value against 21.
-struct Rq8 {
-  bool f32;
-  float s, lo, hi;
-  double ds;
-  RqRange r;
-};
-__device__ __forceinline__ Rq8 make_rq8(const Requant& rq, int act) {
-  Rq8 e;
-  const int32_t am = rq.mult < 0 ? -rq.mult : rq.mult;
-  e.f32 = am > 0 && am <= (1 << 24) && (rq.shift <= 16 || ((int64_t)am << 16) >= ((int64_t)1 << rq.shift));
-  e.ds = rq_scale(rq.mult, rq.shift);
-  e.s = (float)e.ds;
-  e.r = rq_range(rq, act);
-  e.lo = 12582912.0f + (float)(e.r.lo - kRoundF64);  // 1.5 * 2^23
-  e.hi = 12582912.0f + (float)(e.r.hi - kRoundF64);
-  return e;
-}
-// Four results as packed bytes.
-__device__ __forceinline__ uint32_t rq8x4(const i32x4& acc, const Rq8& e) {
-  uint32_t q[4];
-  if (e.f32) {  // (uniform)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int32_t s = acc[v];
-      q[v] = __float_as_uint(__builtin_amdgcn_fmed3f(__builtin_fmaf((float)s, e.s, 12582912.0f), e.lo, e.hi));
-    }
-  } else {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int32_t s = acc[v];
-      q[v] = (uint32_t)rq_round(s, e.ds, e.r);
-    }
-  }
-  return __builtin_amdgcn_perm(q[1], q[0], 0x0c0c0400u) | __builtin_amdgcn_perm(q[3], q[2], 0x04000c0cu);
-}
-
 // Two float results as packed bf16. Without an activation the value passes as it is (a
 // median with infinite ends would turn a NaN into one of them).
 struct EpiF8 {
