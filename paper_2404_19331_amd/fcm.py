@@ -273,12 +273,17 @@ def _torch():
     return torch
 
 
+_DTYPE_NAMES = {}  # torch dtype -> name, filled at the first call (torch is imported late)
+
+
 def _dtype_name(t):
-    torch = _torch()
-    m = {torch.float32: "f32", torch.bfloat16: "bf16", torch.int8: "i8"}
-    if t.dtype not in m:
+    if not _DTYPE_NAMES:
+        torch = _torch()
+        _DTYPE_NAMES.update({torch.float32: "f32", torch.bfloat16: "bf16", torch.int8: "i8"})
+    name = _DTYPE_NAMES.get(t.dtype)
+    if name is None:
         raise TypeError("unsupported dtype %s (float32, bfloat16, int8)" % t.dtype)
-    return m[t.dtype]
+    return name
 
 
 def _dims(x, layout):
@@ -292,7 +297,29 @@ def _dims(x, layout):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# Descriptors of the entry points' calls by their values (never by a tensor), with the plan
+# the planner chose for each: filling the structure and asking for the plan and its workspace
+# are half of a call's host time. Bounded; the entries are read-only once made.
+_DESCS = {}
+_DESCS_MOST = 1024
+
+
+def _desc(n, h, w, ci, cm, co, k, stride, pad, dt, layout, act, rq, rq_channel, zp_in):
+    if rq_channel is not None:
+        return make_desc(n, h, w, ci, cm, co, k, stride, pad, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    key = (n, h, w, ci, cm, co, k, stride, pad, dt, layout, tuple(act),
+           None if rq is None else tuple([tuple(r) for r in rq]), zp_in)
+    d = _DESCS.get(key)
+    if d is None:
+        d = make_desc(n, h, w, ci, cm, co, k, stride, pad, dt, layout, act, rq, zp_in=zp_in)
+        d._plans = {}
+        if len(_DESCS) >= _DESCS_MOST:
+            _DESCS.clear()
+        _DESCS[key] = d
+    return d
 
 
 def _prep(x, tensors, biases, dt):
@@ -325,8 +352,11 @@ def _out(x, layout, n, c, h, w, out):
 
 
 def _stream(x, stream):
-    torch = _torch()
     if stream is None:
+        torch = _torch()
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw is not None:  # (current_stream builds a Stream object around it: 2 us)
+            return raw(x.device.index)
         stream = torch.cuda.current_stream(x.device)
     return ctypes.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
 
@@ -364,9 +394,16 @@ def workspace_bytes(desc, plan):
 def _with_workspace(op, d, x, plan, workspace):
     """The plan to launch (the planner's best when None) and the workspace it needs: the
     caller's tensor, or a fresh one from torch's allocator (the library allocates nothing)."""
-    if plan is None:
-        plan = _find_plan(op, d)
-    need = workspace_bytes(d, plan)
+    plans = getattr(d, "_plans", None) if plan is None else None
+    hit = plans.get(op) if plans is not None else None
+    if hit is None:
+        if plan is None:
+            plan = _find_plan(op, d)
+        need = workspace_bytes(d, plan)
+        if plans is not None:
+            plans[op] = (plan, need)
+    else:
+        plan, need = hit
     if need == 0:
         return plan, None
     torch = _torch()
@@ -400,7 +437,7 @@ def dw_pw(x, w_dw, w_pw, b_dw=None, b_pw=None, *, stride=1, pad=None, act=("none
     pad = (k - 1) // 2 if pad is None else pad
     co = int(w_pw.shape[0])
     _prep(x, [w_dw, w_pw], [b_dw, b_pw], dt)
-    d = make_desc(n, h, w, c, c, co, k, stride, pad, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, c, co, k, stride, pad, dt, layout, act, rq, rq_channel, zp_in)
     ho, wo = out_hw(h, w, k, stride, pad)
     y = _out(x, layout, n, co, ho, wo, out)
     plan, ws = _with_workspace("dw_pw", d, x, plan, workspace)
@@ -426,7 +463,7 @@ def dw_pw_noalloc(x, w_dw, w_pw, b_dw=None, b_pw=None, *, stride=1, pad=None, ac
     pad = (k - 1) // 2 if pad is None else pad
     co = int(w_pw.shape[0])
     _prep(x, [w_dw, w_pw], [b_dw, b_pw], dt)
-    d = make_desc(n, h, w, c, c, co, k, stride, pad, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, c, co, k, stride, pad, dt, layout, act, rq, rq_channel, zp_in)
     ho, wo = out_hw(h, w, k, stride, pad)
     y = _out(x, layout, n, co, ho, wo, out)
     return _call(lib().fcm_dw_pw_noalloc, (ctypes.byref(d), _ptr(x), _ptr(w_dw), _ptr(b_dw), _ptr(w_pw), _ptr(b_pw),
@@ -442,7 +479,7 @@ def pw_dw(x, w_pw, w_dw, b_pw=None, b_dw=None, *, stride=1, pad=None, act=("none
     pad = (k - 1) // 2 if pad is None else pad
     cm = int(w_pw.shape[0])
     _prep(x, [w_pw, w_dw], [b_pw, b_dw], dt)
-    d = make_desc(n, h, w, c, cm, cm, k, stride, pad, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, cm, cm, k, stride, pad, dt, layout, act, rq, rq_channel, zp_in)
     ho, wo = out_hw(h, w, k, stride, pad)
     y = _out(x, layout, n, cm, ho, wo, out)
     return _call(lib().fcm_pw_dw, (ctypes.byref(d), _ptr(x), _ptr(w_pw), _ptr(b_pw), _ptr(w_dw), _ptr(b_dw),
@@ -459,7 +496,7 @@ def pw_dw_pw(x, w_pw1, w_dw, w_pw2, b_pw1=None, b_dw=None, b_pw2=None, *, stride
     pad = (k - 1) // 2 if pad is None else pad
     cm, co = int(w_pw1.shape[0]), int(w_pw2.shape[0])
     _prep(x, [w_pw1, w_dw, w_pw2], [b_pw1, b_dw, b_pw2], dt)
-    d = make_desc(n, h, w, c, cm, co, k, stride, pad, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, cm, co, k, stride, pad, dt, layout, act, rq, rq_channel, zp_in)
     ho, wo = out_hw(h, w, k, stride, pad)
     y = _out(x, layout, n, co, ho, wo, out)
     return _call(lib().fcm_pw_dw_pw, (ctypes.byref(d), _ptr(x), _ptr(w_pw1), _ptr(b_pw1), _ptr(w_dw), _ptr(b_dw),
@@ -474,7 +511,7 @@ def pw_pw(x, w_pw1, w_pw2, b_pw1=None, b_pw2=None, *, act=("none", "none"), rq=N
     n, c, h, w = _dims(x, layout)
     cm, co = int(w_pw1.shape[0]), int(w_pw2.shape[0])
     _prep(x, [w_pw1, w_pw2], [b_pw1, b_pw2], dt)
-    d = make_desc(n, h, w, c, cm, co, 1, 1, 0, dt, layout, act, rq, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, cm, co, 1, 1, 0, dt, layout, act, rq, rq_channel, zp_in)
     y = _out(x, layout, n, co, h, w, out)
     return _call(lib().fcm_pw_pw, (ctypes.byref(d), _ptr(x), _ptr(w_pw1), _ptr(b_pw1), _ptr(w_pw2), _ptr(b_pw2),
                                    _ptr(y), _plan_arg(plan), _stream(x, stream)), y, prepare)
@@ -488,7 +525,7 @@ def dw(x, w_dw, b_dw=None, *, stride=1, pad=None, act="none", rq=None, rq_channe
     k = _kk(w_dw)
     pad = (k - 1) // 2 if pad is None else pad
     _prep(x, [w_dw], [b_dw], dt)
-    d = make_desc(n, h, w, c, c, c, k, stride, pad, dt, layout, (act,), [rq] if rq else None, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, c, c, k, stride, pad, dt, layout, (act,), [rq] if rq else None, rq_channel, zp_in)
     ho, wo = out_hw(h, w, k, stride, pad)
     y = _out(x, layout, n, c, ho, wo, out)
     return _call(lib().fcm_dw, (ctypes.byref(d), _ptr(x), _ptr(w_dw), _ptr(b_dw), _ptr(y), _plan_arg(plan),
@@ -502,7 +539,7 @@ def pw(x, w_pw, b_pw=None, *, act="none", rq=None, rq_channel=None, layout="nchw
     n, c, h, w = _dims(x, layout)
     co = int(w_pw.shape[0])
     _prep(x, [w_pw], [b_pw], dt)
-    d = make_desc(n, h, w, c, c, co, 1, 1, 0, dt, layout, (act,), [rq] if rq else None, rq_channel=rq_channel, zp_in=zp_in)
+    d = _desc(n, h, w, c, c, co, 1, 1, 0, dt, layout, (act,), [rq] if rq else None, rq_channel, zp_in)
     y = _out(x, layout, n, co, h, w, out)
     plan, ws = _with_workspace("pw", d, x, plan, workspace)
     if ws is None:
