@@ -56,7 +56,9 @@ const Variant* all_variants(int* count) {
                                      variants_v5_dwpw_bf16_s1, variants_v5_dwpw_bf16_s2, variants_v5_pwdw_bf16,
                                      variants_v6_f32, variants_v7_bf16, variants_v8_bf16, variants_v8_i8_k3,
                                      variants_v8_i8_k5, variants_v8_bf16_k5, variants_v9_bf16, variants_v9_f32,
-                                     variants_v9_i8};
+                                     variants_v9_i8, variants_v8_nchw_f32_k3, variants_v8_nchw_f32_k5,
+                                     variants_v8_nchw_bf16_k3, variants_v8_nchw_i8_k3,
+                                     variants_v8_f32_k3, variants_v8_f32_k5};
     for (auto fn : fns) {
       int n = 0;
       const Variant* t = fn(&n);

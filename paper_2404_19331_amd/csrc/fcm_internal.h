@@ -475,8 +475,8 @@ struct Variant {
                     //    every channel of every stage in one workgroup
                     // 7: deep DW->PW kernels (bf16, 3x3): compile-time tile of at most 64
                     //    pixels, one compiled output-channel block
-                    // 8: PW->DW(->PW) NHWC kernels (bf16, int8): run-time tile of at most
-                    //    max_p pixels, 64-byte intermediate chunks
+                    // 8: PW->DW(->PW) kernels (NHWC and NCHW): run-time tile of at
+                    //    most max_p pixels, 64-byte intermediate chunks
                     // 9: NCHW DW->PW kernels over window chunks: run-time tile of at most
                     //    max_p pixels, one compiled output-channel block
   int pitch = 0;    // gen 3: LDS window row pitch in pixels (window width must not exceed it)
@@ -485,7 +485,7 @@ struct Variant {
                     // gen 5: LDS ring slots; gen 8: as gen 4
   int wc = 1;       // gen 5: waves across output channels (1, 2 or 4); gens 8 and 9:
                     // 16-pixel blocks per wave
-  int kc = 1;       // gen 7: 32-channel chunks per item (1 or 2)
+  int kc = 1;       // gen 7: 32-channel chunks per item (1 or 2); gen 8: 2 = NCHW
 };
 
 // Compiled variants of each translation unit, and all of them in a fixed order
@@ -514,6 +514,12 @@ const Variant* variants_v8_bf16(int* count);
 const Variant* variants_v8_bf16_k5(int* count);
 const Variant* variants_v8_i8_k3(int* count);
 const Variant* variants_v8_i8_k5(int* count);
+const Variant* variants_v8_f32_k3(int* count);
+const Variant* variants_v8_f32_k5(int* count);
+const Variant* variants_v8_nchw_f32_k3(int* count);
+const Variant* variants_v8_nchw_f32_k5(int* count);
+const Variant* variants_v8_nchw_bf16_k3(int* count);
+const Variant* variants_v8_nchw_i8_k3(int* count);
 const Variant* variants_v9_bf16(int* count);
 const Variant* variants_v9_f32(int* count);
 const Variant* variants_v9_i8(int* count);

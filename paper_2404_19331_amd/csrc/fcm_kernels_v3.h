@@ -623,7 +623,7 @@ __global__ __launch_bounds__(kThreads3) void k_fused3(KArgs a) {
               }
             } else {
 #pragma unroll
-              for (int b = 0; b < NB; ++b) bop[b][q] = rq8x4(dacc[b], rq_dw);
+              for (int b = 0; b < NB; ++b) bop[b][q] = rq8x4<true>(dacc[b], rq_dw);
             }
             // (one slot's operands live at a time: scheduled together the four spill)
             __builtin_amdgcn_sched_barrier(0);

@@ -1,6 +1,6 @@
-// fcm_kernels_v8.h -- PW->DW and PW->DW->PW modules on NHWC, bf16 and int8 (gfx950).
+// fcm_kernels_v8.h -- PW->DW and PW->DW->PW modules (gfx950), NHWC and NCHW.
 //
-// k_ir8<DT, K, KS, CT, PB>
+// k_ir8<DT, K, KS, CT, PB, NCHW>
 //   A workgroup computes one TH x TW output tile (run time) of one image. The intermediate
 //   channels go through it in chunks of MC = 64 bytes (one MFMA k-step of the last
 //   convolution): the first PW expands a chunk on the tile's haloed window into an LDS
@@ -30,6 +30,10 @@
 //     bytes to store, or the B operand of PW2. (Integer zeros cannot pick up a NaN or
 //     infinity of a neighbouring channel, so only int8 can use the diagonal form.)
 //   * PW2: the DW result is the MFMA's B operand without leaving the registers.
+//
+//   NCHW gathers the window transposed, one element load per channel and position (lanes
+//   along the pixels of a plane), and stores each channel's pixels to its plane; all between
+//   is the same. fp32: 16-channel chunks, four 16x16x4 MFMAs a k-step, FMA stencils.
 //
 //   E and the window have a pitch of 16 bytes more than a multiple of 64, an odd number of
 //   16-byte units: 16 lanes at consecutive positions reach every LDS bank once.
@@ -69,6 +73,38 @@ __device__ __forceinline__ u32x4 load_row8(rsrc_t r, bool vec, uint32_t voff, ui
   for (int e = 0; e < 4; ++e)
     v[e] = __builtin_amdgcn_raw_buffer_load_b32(r, 4 * e < nb ? voff + 4 * e : kOob, soff, 0);
   return v;
+}
+
+// One element of a buffer as a 32-bit value (bf16 bits, int8 byte, fp32 bits).
+template <class DT>
+__device__ __forceinline__ uint32_t load_elem8(rsrc_t r, uint32_t voff, uint32_t soff) {
+  if constexpr (DT::ELT == 4) return __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
+  else if constexpr (DT::ELT == 2) return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
+  else return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, voff, soff, 0);
+}
+// The 16 / ELT elements of a slot packed into 16 bytes.
+template <class DT>
+__device__ __forceinline__ u32x4 pack_slot8(const uint32_t (&v)[16 / DT::ELT]) {
+  u32x4 o;
+#pragma unroll
+  for (int d = 0; d < 4; ++d) {
+    if constexpr (DT::ELT == 4) o[d] = v[d];
+    else if constexpr (DT::ELT == 2) o[d] = v[2 * d] | (v[2 * d + 1] << 16);
+    else o[d] = v[4 * d] | (v[4 * d + 1] << 8) | (v[4 * d + 2] << 16) | (v[4 * d + 3] << 24);
+  }
+  return o;
+}
+
+// The first `valid` of N packed elements, one to each of consecutive planes.
+template <class DT, int N>
+__device__ __forceinline__ void store_planes8(char* y, size_t plane, const u32x4& o, int valid) {
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    if (q >= valid) break;
+    if constexpr (DT::ELT == 4) *(uint32_t*)(y + q * plane) = o[q];
+    else if constexpr (DT::ELT == 2) *(uint16_t*)(y + q * plane) = (uint16_t)(o[q >> 1] >> (16 * (q & 1)));
+    else *(uint8_t*)(y + q * plane) = (uint8_t)(o[q >> 2] >> (8 * (q & 3)));
+  }
 }
 
 // The depthwise stage of one wave: lane = output pixel l % 16 of each of PB blocks, slot
@@ -189,10 +225,10 @@ struct DwLanes8 {
   }
 };
 
-template <class DT, int K, int KS, int CT, int PB>
+template <class DT, int K, int KS, int CT, int PB, bool NCHW>
 __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
   extern __shared__ __align__(16) char smem[];
-  constexpr bool I8 = std::is_same<DT, TI8>::value;
+  constexpr bool I8 = std::is_same<DT, TI8>::value, F32 = std::is_same<DT, TF32>::value;
   using AccV = typename DT::AccV;
   constexpr int E = DT::ELT, MC = 64 / E, TPC = 4 / E, CPG = 16 / E;
   constexpr int KK = K * K;
@@ -274,12 +310,20 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
 #pragma unroll
       for (int b = 0; b < B; ++b) {
         const int i = i0 + b * step;
-        const int pos = i / nsl, sl = i - pos * nsl;
+        const int pos = NCHW ? i % lay.nqp : i / nsl, sl = NCHW ? i / lay.nqp : i - pos * nsl;
         const int qy = pos / IW, qx = pos - qy * IW;
         const int gy = iy0 + qy, gx = ix0 + qx;
         const bool ok = pos < Q && (unsigned)gy < (unsigned)a.H && (unsigned)gx < (unsigned)a.W;
         dst[b] = i < items ? pos * lay.xp + sl * 16 : -1;
-        v[b] = load_row8(rx, a.vec_x, (uint32_t)((gy * a.W + gx) * ci_b + sl * 16), 0u, ok ? ci_b - sl * 16 : 0);
+        if constexpr (NCHW) {  // (channels beyond the last lie beyond the image's buffer)
+          uint32_t el[CPG];
+          const uint32_t off = ok ? (uint32_t)(((sl * CPG * a.H + gy) * a.W + gx) * E) : kOob;
+#pragma unroll
+          for (int e = 0; e < CPG; ++e) el[e] = load_elem8<DT>(rx, off, (uint32_t)(e * a.H * a.W * E));
+          v[b] = pack_slot8<DT>(el);
+        } else {
+          v[b] = load_row8(rx, a.vec_x, (uint32_t)((gy * a.W + gx) * ci_b + sl * 16), 0u, ok ? ci_b - sl * 16 : 0);
+        }
       }
 #pragma unroll
       for (int b = 0; b < B; ++b)
@@ -362,6 +406,12 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
         if constexpr (I8) {
 #pragma unroll
           for (int tt = 0; tt < TPC; ++tt) o[tt] = rq8x4(acc[tt], q1);
+        } else if constexpr (F32) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float f = acc[0][q];
+            o[q] = __float_as_uint(e1.none ? f : __builtin_amdgcn_fmed3f(f, e1.lo, e1.hi));
+          }
         } else {
 #pragma unroll
           for (int tt = 0; tt < TPC; ++tt)
@@ -394,8 +444,13 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
         const int ch = m0 + CPG * g;
 #pragma unroll
         for (int b = 0; b < PB; ++b)
-          if (opix[b] >= 0 && ch < mb)
-            *(u32x4*)((char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Cm + cm0 + ch) * E) = d[b];
+          if (opix[b] >= 0 && ch < mb) {
+            if constexpr (NCHW)
+              store_planes8<DT, CPG>((char*)a.y + (((size_t)n * a.Cm + cm0 + ch) * a.Ho * a.Wo + opix[b]) * E,
+                                     (size_t)a.Ho * a.Wo * E, d[b], mb - ch);
+            else
+              *(u32x4*)((char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Cm + cm0 + ch) * E) = d[b];
+          }
       }
     }
   }
@@ -429,26 +484,41 @@ __global__ __launch_bounds__(64 * kMaxWaves8) void k_ir8(KArgs a) {
       if (co >= a.Co) continue;
       AccV bb;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) bb[q] = load_bias<DT>(a.b3, co + q);
+      for (int q = 0; q < 4; ++q) bb[q] = load_bias<DT>(a.b3, min(co + q, a.Co - 1));
 #pragma unroll
       for (int b = 0; b < PB; ++b) {
         const AccV v = acc2[b][u] + bb;
-        char* y = (char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Co + co) * E;
+        u32x4 o = {0u, 0u, 0u, 0u};  // the four results, packed from word 0
         if constexpr (I8) {
-          const uint32_t o = rq8x4(v, q3);
-          if (opix[b] >= 0) *(uint32_t*)y = o;
+          o[0] = rq8x4(v, q3);
+        } else if constexpr (F32) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const float f = v[q];
+            o[q] = __float_as_uint(e3.none ? f : __builtin_amdgcn_fmed3f(f, e3.lo, e3.hi));
+          }
         } else {
-          const u32x2 o = {bf16x2_8(v[0], v[1], e3), bf16x2_8(v[2], v[3], e3)};
-          if (opix[b] >= 0) *(u32x2*)y = o;
+          o[0] = bf16x2_8(v[0], v[1], e3);
+          o[1] = bf16x2_8(v[2], v[3], e3);
+        }
+        if (opix[b] < 0) continue;
+        if constexpr (NCHW) {
+          store_planes8<DT, 4>((char*)a.y + (((size_t)n * a.Co + co) * a.Ho * a.Wo + opix[b]) * E,
+                               (size_t)a.Ho * a.Wo * E, o, a.Co - co);
+        } else {
+          char* y = (char*)a.y + (((size_t)n * a.Ho * a.Wo + opix[b]) * a.Co + co) * E;
+          if constexpr (I8) *(uint32_t*)y = o[0];
+          else if constexpr (F32) *(u32x4*)y = o;
+          else *(u32x2*)y = u32x2{o[0], o[1]};
         }
       }
     }
   }
 }
 
-template <class DT, int K, int KS, int CT, int PB>
+template <class DT, int K, int KS, int CT, int PB, bool NCHW>
 int launch_ir8(const KArgs& a, int grid, void* stream) {
-  const void* fn = (const void*)k_ir8<DT, K, KS, CT, PB>;
+  const void* fn = (const void*)k_ir8<DT, K, KS, CT, PB, NCHW>;
   const int lds = a.L.bytes;
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);

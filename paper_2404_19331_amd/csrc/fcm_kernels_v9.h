@@ -29,26 +29,6 @@
 
 namespace fcm {
 
-// One element of a buffer as a 32-bit value (bf16 bits, int8 byte, fp32 bits).
-template <class DT>
-__device__ __forceinline__ uint32_t load_elem9(rsrc_t r, uint32_t voff, uint32_t soff) {
-  if constexpr (DT::ELT == 4) return __builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0);
-  else if constexpr (DT::ELT == 2) return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, voff, soff, 0);
-  else return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(r, voff, soff, 0);
-}
-// The 16 / ELT elements of a slot packed into 16 bytes.
-template <class DT>
-__device__ __forceinline__ u32x4 pack_slot9(const uint32_t (&v)[16 / DT::ELT]) {
-  u32x4 o;
-#pragma unroll
-  for (int d = 0; d < 4; ++d) {
-    if constexpr (DT::ELT == 4) o[d] = v[d];
-    else if constexpr (DT::ELT == 2) o[d] = v[2 * d] | (v[2 * d + 1] << 16);
-    else o[d] = v[4 * d] | (v[4 * d + 1] << 8) | (v[4 * d + 2] << 16) | (v[4 * d + 3] << 24);
-  }
-  return o;
-}
-
 // How the rows of a matrix can be read: whole 16 bytes, words, or elements.
 enum { ROWS_VEC = 0, ROWS_WORDS = 1, ROWS_ELEMENTS = 2 };
 
@@ -121,7 +101,7 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
 #pragma unroll
       for (int e = 0; e < CPG; ++e) {
         const int ch = I8 ? 16 * (e >> 2) + (e & 3) : e;  // (from the slot's first channel)
-        xr[k][e] = load_elem9<DT>(rx, xoff[k], so + (uint32_t)(ch * hw * E));
+        xr[k][e] = load_elem8<DT>(rx, xoff[k], so + (uint32_t)(ch * hw * E));
       }
     }
     const int left = ci_b - c * 64 - 16 * (gt & 3);  // bytes of the row from this lane's slot on
@@ -134,8 +114,8 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
         uint32_t v[CPG];
 #pragma unroll
         for (int e = 0; e < CPG; ++e)
-          v[e] = load_elem9<DT>(rw, e * E < left ? woff[k] + e * E : kOob, (uint32_t)(c * 64));
-        wr[k] = pack_slot9<DT>(v);
+          v[e] = load_elem8<DT>(rw, e * E < left ? woff[k] + e * E : kOob, (uint32_t)(c * 64));
+        wr[k] = pack_slot8<DT>(v);
       }
     }
   };
@@ -143,7 +123,7 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
 #pragma unroll
     for (int k = 0; k < NX; ++k) {
       if (k * ng >= 4 * lay.nqp) break;
-      if (xdst[k] >= 0) *(u32x4*)(eb + xdst[k]) = pack_slot9<DT>(xr[k]);
+      if (xdst[k] >= 0) *(u32x4*)(eb + xdst[k]) = pack_slot8<DT>(xr[k]);
     }
 #pragma unroll
     for (int k = 0; k < NWV; ++k) {
@@ -159,7 +139,7 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
     const rsrc_t rd = make_rsrc(a.w1, (uint32_t)(real * E));
     const rsrc_t rb = make_rsrc(a.b1 ? a.b1 : a.w1, a.b1 ? (uint32_t)(a.Ci * 4) : 0u);
     for (int i = threadIdx.x; i < nel; i += 64 * nw) {
-      const uint32_t v = load_elem9<DT>(rd, i < real ? (uint32_t)(i * E) : kOob, 0u);
+      const uint32_t v = load_elem8<DT>(rd, i < real ? (uint32_t)(i * E) : kOob, 0u);
       char* p = smem + lay.dww_off + i * E;
       if constexpr (E == 4) *(uint32_t*)p = v;
       else if constexpr (E == 2) *(uint16_t*)p = (uint16_t)v;
@@ -243,7 +223,7 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
 #pragma unroll
     for (int b = 0; b < PB; ++b) {
       const AccV v = acc2[b][u] + bb;
-      uint32_t o[4];  // 16 bytes: the four values (fp32), else packed in o[0], o[1]
+      u32x4 o = {0u, 0u, 0u, 0u};  // the four results, packed from word 0
       if constexpr (I8) {
         o[0] = rq8x4(v, q2);
       } else if constexpr (F32) {
@@ -257,15 +237,8 @@ __global__ __launch_bounds__(256) void k_dwpw9(KArgs a) {
         o[1] = bf16x2_8(v[2], v[3], e2);
       }
       if (opix[b] < 0) continue;
-      char* y = (char*)a.y + (((size_t)n * a.Co + co) * a.Ho * a.Wo + opix[b]) * E;
-      const size_t plane = (size_t)a.Ho * a.Wo * E;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (co + q >= a.Co) break;
-        if constexpr (F32) *(uint32_t*)(y + q * plane) = o[q];
-        else if constexpr (I8) *(uint8_t*)(y + q * plane) = (uint8_t)(o[0] >> (8 * q));
-        else *(uint16_t*)(y + q * plane) = (uint16_t)(o[q >> 1] >> (16 * (q & 1)));
-      }
+      store_planes8<DT, 4>((char*)a.y + (((size_t)n * a.Co + co) * a.Ho * a.Wo + opix[b]) * E,
+                           (size_t)a.Ho * a.Wo * E, o, a.Co - co);
     }
   }
 }

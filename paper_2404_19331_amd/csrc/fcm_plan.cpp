@@ -384,14 +384,15 @@ static fcm_status evaluate_plan4(const Variant& v, const Geom& g, const fcm_hw_d
 static fcm_status evaluate_plan8(const Variant& v, const Geom& g, const fcm_hw_desc& hw, fcm_plan_t* p) {
   const int e = g.elt, mc = 64 / e;
   const bool last_pw = g.family == FAM_PWDWPW;
-  if (g.layout != FCM_NHWC) return fail(FCM_EUNSUPPORTED, "plan: the kernel needs NHWC");
-  if ((g.ci * e) % 4 || (g.cm * e) % 16 || (last_pw && g.co % 4))
-    return fail(FCM_EUNSUPPORTED, "plan: the kernel needs 4-byte input rows, 16-byte intermediate rows and output "
-                                  "channels in fours");
+  const bool nchw = v.kc == 2;
+  if (g.layout != (nchw ? FCM_NCHW : FCM_NHWC)) return fail(FCM_EUNSUPPORTED, "plan: the kernel is of the other layout");
+  if ((g.ci * e) % 4 || (g.cm * e) % 16 || (last_pw && g.co % 4 && !nchw))
+    return fail(FCM_EUNSUPPORTED, "plan: the kernel needs 4-byte weight rows, 16-byte intermediate rows and (NHWC) "
+                                  "output channels in fours");
   if (g.ci * e > 64 * v.ks || (last_pw && g.co > v.max_cob))
     return fail(FCM_EUNSUPPORTED, "plan: channels exceed what the kernel variant holds in registers");
   const int64_t lim = (int64_t)1 << 30;  // 32-bit buffer offsets with room for an out-of-range scalar part
-  if ((int64_t)g.h * g.w * g.ci * e >= lim || (int64_t)(g.cm + mc) * g.ci * e >= lim ||
+  if ((int64_t)g.h * g.w * (g.ci + mc) * e >= lim || (int64_t)(g.cm + mc) * g.ci * e >= lim ||
       (int64_t)(g.co + 16) * g.cm * e >= lim)
     return fail(FCM_EUNSUPPORTED, "plan: tensor too large for the kernel");
   const int TH = p->tile_h, TW = p->tile_w, P = TH * TW;
@@ -403,8 +404,8 @@ static fcm_status evaluate_plan8(const Variant& v, const Geom& g, const fcm_hw_d
   if (last_pw ? p->co_block != round_up(g.co, 16) : (p->co_block <= 0 || p->co_block % mc || p->co_block > round_up(g.cm, mc)))
     return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
   const int mb = last_pw ? g.cm : p->co_block;
-  if (gw * groups > 8 || groups > ceil_div(mb, mc) || (groups & (groups - 1)))
-    return fail(FCM_EUNSUPPORTED, "plan: 1, 2, 4 or 8 groups of at most eight waves and one chunk each");
+  if (gw * groups > (nchw ? 4 : 8) || groups > ceil_div(mb, mc) || (groups & (groups - 1)))
+    return fail(FCM_EUNSUPPORTED, "plan: 1, 2, 4 or 8 groups of at most eight waves (NCHW: four) and one chunk each");
   const Lds8 L = lds8(g.dtype, g.k, g.s, TH, TW, g.ci, mb, gw, groups, v.wc, v.max_cob / 16);
   if (L.total > hw.lds_per_wg) return fail(FCM_EUNSUPPORTED, "plan: tiling exceeds the LDS per workgroup");
   const int64_t wgs = (int64_t)g.n * ceil_div(g.ho, TH) * ceil_div(g.wo, TW) * (last_pw ? 1 : ceil_div(g.cm, p->co_block));
@@ -775,7 +776,9 @@ static double small_time_estimate(const Variant& v, const Geom& g, const fcm_pla
   const double xpt = ceil_div(IH * IW * ci16 * 16, 256);
   const int per_cu = std::max(1, std::min(8, (int)(hw.lds_per_cu / std::max(1, (int)p.lds_bytes))));
   const double rounds = std::ceil((double)std::max(1, (int)p.workgroups) / ((double)per_cu * hw.num_cus));
-  return kLaunch + rounds * (kFixed + kPerMfma * mfma + kPerWindowElt * xpt) / kClock;
+  // (with a first PW the timings of other shapes than C2's lie 1.05-1.5x over the fit: 28x28
+  // 32->192->32 10.9 us for 9.2, 101x101 16->48->16 11.3 for 7.5)
+  return (pw1 ? 1.25 : 1.0) * (kLaunch + rounds * (kFixed + kPerMfma * mfma + kPerWindowElt * xpt) / kClock);
 }
 
 // Time model of the deep DW->PW kernels (gen 7), in seconds: the launch with the first
@@ -816,7 +819,8 @@ static double ir_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t
   constexpr double kLaunch = 1.5e-6, kClock = 2.4e9, kStart = 6730.0, kIter = 1670.0, kAlone = 0.73, kShared = 0.306,
                    kMfma = 81.0, kWave = 56.0, kExchange = 138.0, kStage = 490.0;
   const bool i8 = g.elt == 1;
-  const double kTile = i8 ? 969.0 : 167.0, kBlock = i8 ? 159.0 : 872.0, kTaps = i8 ? 277.0 : 0.0;
+  const bool f32 = g.elt == 4;  // (four MFMAs a k-step; its figures from a few timed plans)
+  const double kTile = i8 ? 969.0 : (f32 ? 100.0 : 167.0), kBlock = i8 ? 159.0 : 872.0, kTaps = i8 ? 277.0 : 0.0;
   const int mc = 64 / g.elt, gw = waves8(p.tile_h * p.tile_w, v.wc), groups = std::max(1, (int)p.splits);
   const bool pw2 = g.family == FAM_PWDWPW;
   const int mb = pw2 ? g.cm : std::min(p.co_block, g.cm);
@@ -824,7 +828,7 @@ static double ir_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t
   const int ks = ceil_div(g.ci * g.elt, 64), nkk = ceil_div(g.k * g.k, 4);
   const double nqt = ceil_div(ceil_div(q, 16), gw), ct = pw2 ? ceil_div(g.co, 16) : 0;
   const double iters = ceil_div(ceil_div(mb, mc), groups), nw = gw * groups;
-  const double mfma = 4 / g.elt * ks * nqt + ct * v.wc + (i8 ? 4 * nkk * v.wc : 0);
+  const double mfma = f32 ? 2 * (ks * nqt + ct * v.wc) : 4 / g.elt * ks * nqt + ct * v.wc + (i8 ? 4 * nkk * v.wc : 0);
   const double valu = nqt * kTile + v.wc * kBlock + kTaps * (nkk - 3) + kMfma * mfma;
   const int fit = std::min(hw.lds_per_cu / std::max(1, (int)p.lds_bytes), (int)(12 / nw));
   const double per_cu = std::max(1, fit);

@@ -1,4 +1,5 @@
-"""GPU parity of the PW -> DW (-> PW) NHWC kernels (k_ir8), forced through explicit plans.
+"""GPU parity of the PW -> DW (-> PW) kernels (k_ir8, NHWC and NCHW), forced through explicit
+plans.
 
 Every compiled variant that implements a case runs over tiles that leave ragged pixel
 blocks, window tiles and image borders, with one and several groups of waves sharing a
@@ -17,7 +18,7 @@ from gpu_util import assert_close, dev_inputs, oracle_ref, run_fused, to_np
 
 pytestmark = pytest.mark.gpu
 
-ELT = {"bf16": 2, "i8": 1}
+ELT = {"f32": 4, "bf16": 2, "i8": 1}
 # (multiplier, shift, range): a power of two, a 15-bit and a 31-bit multiplier (the last not
 # a single-precision value), about the same scales
 RQ = ((1, 7, -127, 127), (20011, 22, -128, 127), (1342177283, 38, -127, 127))
@@ -26,19 +27,27 @@ RQ = ((1, 7, -127, 127), (20011, 22, -128, 127), (1342177283, 38, -127, 127))
 def _cases():
     out = []
     shapes = {  # c_in, c_mid, c_out, k, stride, pad
-        "bf16": [(24, 144, 24, 3, 1, 1), (40, 72, 20, 3, 2, 1), (24, 96, 20, 5, 1, 2), (70, 136, 68, 5, 2, 2), (50, 64, 36, 3, 1, 0), (160, 200, 160, 3, 2, 2),
-                 (8, 16, 4, 3, 1, 1), (96, 576, 96, 3, 1, 1)],
+        "f32": [(24, 144, 24, 3, 1, 1), (23, 36, 20, 5, 2, 1), (90, 64, 96, 3, 2, 2)],
+        "bf16": [(24, 144, 24, 3, 1, 1), (40, 72, 20, 3, 2, 1), (24, 96, 20, 5, 1, 2), (70, 136, 68, 5, 2, 2),
+                 (50, 64, 36, 3, 1, 0), (160, 200, 160, 3, 2, 2), (8, 16, 4, 3, 1, 1), (96, 576, 96, 3, 1, 1)],
         "i8": [(24, 144, 24, 3, 1, 1), (36, 64, 20, 3, 2, 1), (160, 208, 160, 5, 1, 2), (64, 384, 64, 3, 1, 0),
                (16, 48, 4, 5, 2, 4), (100, 320, 96, 3, 2, 2)],
     }
-    for dt, shp in shapes.items():
-        for ci, cm, co, k, s, pad in shp:
-            for op in ("pw_dw", "pw_dw_pw"):
-                act = [("relu6", "relu", "none"), ("none", "relu6", "relu")][len(out) // 2 % 2]
-                out.append(Case(op, 2, 13, 11, ci, cm, co if op == "pw_dw_pw" else cm, k, s, pad, dt, "nhwc", act,
-                                RQ[len(out) % 3:] + RQ[:len(out) % 3], dist_x="i8small" if dt == "i8" else "n01",
-                                dist_w="i8small", bias=True, seed=4100 + len(out),
-                                name="v8-%s-%s-%d-%d-%d-k%ds%dp%d" % (op, dt, ci, cm, co, k, s, pad)))
+    nchw = {
+        "f32": [(24, 144, 24, 3, 1, 1), (23, 36, 30, 3, 2, 1), (96, 64, 17, 3, 1, 0), (50, 100, 64, 5, 1, 2),
+                (16, 20, 7, 5, 2, 4)],
+        "bf16": [(24, 144, 24, 3, 1, 1), (150, 200, 37, 3, 2, 2)],
+        "i8": [(24, 144, 24, 3, 1, 1), (100, 320, 33, 3, 2, 1)],
+    }
+    every = [(dt, "nhwc", sh) for dt, shp in shapes.items() for sh in shp]
+    every += [(dt, "nchw", sh) for dt, shp in nchw.items() for sh in shp]
+    for dt, layout, (ci, cm, co, k, s, pad) in every:
+        for op in ("pw_dw", "pw_dw_pw"):
+            act = [("relu6", "relu", "none"), ("none", "relu6", "relu")][len(out) // 2 % 2]
+            out.append(Case(op, 2, 13, 11, ci, cm, co if op == "pw_dw_pw" else cm, k, s, pad, dt, layout, act,
+                            RQ[len(out) % 3:] + RQ[:len(out) % 3], dist_x="i8small" if dt == "i8" else "n01",
+                            dist_w="i8small", bias=True, seed=4100 + len(out),
+                            name="v8-%s-%s-%s-%d-%d-%d-k%ds%dp%d" % (op, dt, layout, ci, cm, co, k, s, pad)))
     return out
 
 
@@ -51,7 +60,8 @@ def _plans(case):
     nch = -(-case.c_mid // mc)
     plans = []
     for v in range(fcm.lib().fcm_variant_count()):
-        if not fcm.variant_name(v).startswith("k_ir8<%s,%d,%d," % (case.dtype, case.k, case.stride)):
+        kernel = "k_ir8" if case.layout == "nhwc" else "k_pwdw8" if case.op == "pw_dw" else "k_pwdwpw8"
+        if not fcm.variant_name(v).startswith("%s<%s,%d,%d," % (kernel, case.dtype, case.k, case.stride)):
             continue
         for th, tw in ((7, 7), (8, 16), (3, 5), (1, 11), (4, 4), (13, 2)):
             for groups in (1, 2, 8):
@@ -80,7 +90,7 @@ def test_every_variant_tile_and_group(case):
 
 
 def test_planner_takes_them_and_leaves_the_rest():
-    case = CASES[0]
+    case = next(c for c in CASES if c.dtype == "bf16")
     assert fcm.variant_name(fcm.plan("pw_dw", fcm.desc_from_case(case)).variant).startswith("k_ir8")
     for other in (case.with_(layout="nchw"), case.with_(c_mid=143, c_out=143), case.with_(c_in=25)):
         assert not fcm.variant_name(fcm.plan("pw_dw", fcm.desc_from_case(other)).variant).startswith("k_ir8")
