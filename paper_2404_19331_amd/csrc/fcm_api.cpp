@@ -58,7 +58,7 @@ const Variant* all_variants(int* count) {
                                      variants_v8_i8_k5, variants_v8_bf16_k5, variants_v9_bf16, variants_v9_f32,
                                      variants_v9_i8, variants_v8_nchw_f32_k3, variants_v8_nchw_f32_k5,
                                      variants_v8_nchw_bf16_k3, variants_v8_nchw_i8_k3,
-                                     variants_v8_f32_k3, variants_v8_f32_k5};
+                                     variants_v8_f32_k3, variants_v8_f32_k5, variants_v10_bf16};
     for (auto fn : fns) {
       int n = 0;
       const Variant* t = fn(&n);

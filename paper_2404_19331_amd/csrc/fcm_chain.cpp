@@ -157,10 +157,14 @@ fcm_status fcm_chain_plan(const fcm_chain_desc* chain, int32_t objective, const 
       // bf16: a sum that the PW->DW(->PW) kernels round differently (1e-5 of the values)
       // travels through all layers that follow, and after MobileNetV2's 51 the outputs are
       // 3.3e-3 off the other kernels', beyond the 2e-3 a bf16 chain is held to: bf16 chains
-      // keep the kernels that agree when planned by time (batch 1: 287 us, with them 208 us;
-      // by bytes the module planner's plans are taken as they are). int8 chains are exact on
-      // any kernel.
+      // keep the kernels that agree when planned by time (the others can still be put in a
+      // chain plan explicitly; by bytes the module planner's plans are taken as they are).
+      // int8 chains are exact on any kernel.
       const bool same = objective == FCM_CHAIN_TIME && d.dtype == FCM_BF16;
+      // The kernels for few pixels give the bits of the deep kernels (the persistent ones add
+      // the taps one by one, one output in 1e5 differs), and a PW->PW kernel rounds differently
+      // from its two layers apart: the layers are grouped without them, and a deep kernel's
+      // group then takes them where they are faster, so that a chain's outputs stay the same.
       const int kset = kernel_set(op, &d) | (same ? KSET_SAME_ROUNDING : 0);
       st = find_plan(op, &d, &H, &o.plan, kset, 0);
       if (st != FCM_OK) {
@@ -192,7 +196,17 @@ fcm_status fcm_chain_plan(const fcm_chain_desc* chain, int32_t objective, const 
   out->objective = objective;
   int g = 0;
   for (int i = 0; i < n;) {
-    const Opt& o = opts[i][pick[i]];
+    Opt& o = opts[i][pick[i]];
+    int nv = 0;
+    if (objective == FCM_CHAIN_TIME && o.op == FCM_OP_DW_PW && all_variants(&nv)[o.plan.variant].gen == 7) {
+      fcm_desc d;
+      st = chain_group_desc(chain, h.data(), w.data(), ch.data(), i, o.op, &d);
+      if (st != FCM_OK) return st;
+      st = find_plan(o.op, &d, &H, &o.plan,
+                     kernel_set(o.op, &d) | (d.dtype == FCM_BF16 ? KSET_SAME_ROUNDING | KSET_FEW : 0), 0);
+      if (st != FCM_OK) return st;
+      o.time = plan_time_estimate(geometry(o.op, &d), o.plan, H);
+    }
     out->first[g] = i;
     out->op[g] = o.op;
     out->plan[g] = o.plan;

@@ -21,7 +21,11 @@ fcm_status fail(fcm_status st, const std::string& msg);
 // persistent kernels only.
 // KSET_SAME_ROUNDING (a flag): not the PW->DW(->PW) kernels, whose sums round differently
 // from the other kernels' now and then.
-enum { KSET_FIRST = 0, KSET_DMA = 1, KSET_REG = 2, KSET_ALL = 3, KSET_PC = 4, KSET_SAME_ROUNDING = 8 };
+// KSET_FEW (a flag of a search): also the DW->PW kernels for few pixels. Only the time
+// plans of chains ask for them; a module's plan takes them where a caller times the
+// candidates or names the variant.
+enum { KSET_FIRST = 0, KSET_DMA = 1, KSET_REG = 2, KSET_ALL = 3, KSET_PC = 4, KSET_SAME_ROUNDING = 8,
+       KSET_FEW = 16 };
 // The set an int8 descriptor's features allow: per-channel requantisation -> KSET_PC;
 // zero points -> KSET_REG; else all.
 int kernel_set(int op, const fcm_desc* d);

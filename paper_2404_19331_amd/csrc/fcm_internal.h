@@ -444,7 +444,7 @@ struct KArgs {
   int grid_cap;  // persistent kernels: at most this many workgroups (0 = no cap)
   const int32_t* rqc[3];  // int8 per-channel requantisation per stage ([2][channels]) or nullptr
   int zin[3];             // int8 zero point of each stage's input
-  int stride;             // depthwise stride (gens 8 and 9; a template argument elsewhere)
+  int stride;             // depthwise stride (gens 8 to 10; a template argument elsewhere)
   int gw;                 // gens 8 and 9: waves per group
 };
 
@@ -479,12 +479,14 @@ struct Variant {
                     //    most max_p pixels, 64-byte intermediate chunks
                     // 9: NCHW DW->PW kernels over window chunks: run-time tile of at most
                     //    max_p pixels, one compiled output-channel block
+                    // 10: NHWC bf16 DW->PW kernels for few pixels: max_p consecutive
+                    //    pixels of the batch (tile 1 x max_p), one output-channel block
   int pitch = 0;    // gen 3: LDS window row pitch in pixels (window width must not exceed it)
   int ks = 1;       // gen 3: 64-byte channel chunks per item; gen 4: 64-byte k-steps of the
                     // first convolution held in registers (input channels <= 64 * ks bytes);
                     // gen 5: LDS ring slots; gen 8: as gen 4
   int wc = 1;       // gen 5: waves across output channels (1, 2 or 4); gens 8 and 9:
-                    // 16-pixel blocks per wave
+                    // 16-pixel blocks per wave; gen 10: per workgroup
   int kc = 1;       // gen 7: 32-channel chunks per item (1 or 2); gen 8: 2 = NCHW
 };
 
@@ -520,6 +522,7 @@ const Variant* variants_v8_nchw_f32_k3(int* count);
 const Variant* variants_v8_nchw_f32_k5(int* count);
 const Variant* variants_v8_nchw_bf16_k3(int* count);
 const Variant* variants_v8_nchw_i8_k3(int* count);
+const Variant* variants_v10_bf16(int* count);
 const Variant* variants_v9_bf16(int* count);
 const Variant* variants_v9_f32(int* count);
 const Variant* variants_v9_i8(int* count);

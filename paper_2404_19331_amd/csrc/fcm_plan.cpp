@@ -303,7 +303,7 @@ bool variant_needs_alignment(int variant) {
 // tiles; with per-channel requantisation (KSET_PC) the int8 persistent kernels.
 static bool in_set(const Variant& v, int kset) {
   if (v.gen < 2) return true;
-  if ((kset & KSET_SAME_ROUNDING) && v.gen >= 8) return false;
+  if ((kset & KSET_SAME_ROUNDING) && (v.gen == 8 || v.gen == 9)) return false;
   if (kset == KSET_PC) return v.gen == 3 && v.dtype == DT_I8;
   if (kset & KSET_DMA) return true;
   if (!(kset & KSET_REG)) return false;
@@ -458,6 +458,35 @@ static fcm_status evaluate_plan9(const Variant& v, const Geom& g, const fcm_hw_d
   return FCM_OK;
 }
 
+// Plan of the DW->PW kernels for few pixels: its tiling is fixed by the variant (max_p
+// consecutive output pixels of the batch, the compiled output-channel block).
+static fcm_status evaluate_plan10(const Variant& v, const Geom& g, const fcm_hw_desc& hw, fcm_plan_t* p) {
+  if (g.layout != FCM_NHWC) return fail(FCM_EUNSUPPORTED, "plan: the kernel needs NHWC");
+  if (g.ci % 8 || g.co % 8) return fail(FCM_EUNSUPPORTED, "plan: the kernel needs channels in eights");
+  const int64_t lim = (int64_t)1 << 30;  // 32-bit buffer offsets with room for an out-of-range scalar part
+  if ((int64_t)g.n * g.h * g.w * g.ci * 2 >= lim || (int64_t)(g.co + v.max_cob) * g.ci * 2 >= lim ||
+      (int64_t)g.n * g.ho * g.wo >= lim)
+    return fail(FCM_EUNSUPPORTED, "plan: tensor too large for the kernel");
+  if (p->tile_h != 1 || p->tile_w != v.max_p || p->c_block != 32 || p->co_block != v.max_cob || p->splits > 1)
+    return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
+  const int lds = v.wc * ceil_div(g.ci, 32) * 1024;
+  if (lds > hw.lds_per_wg) return fail(FCM_EUNSUPPORTED, "plan: tiling exceeds the LDS per workgroup");
+  const int64_t wgs = ceil_div((int64_t)g.n * g.ho * g.wo, (int64_t)v.max_p) * ceil_div(g.co, v.max_cob);
+  if (wgs > 0x7fffffff) return fail(FCM_EUNSUPPORTED, "plan: grid too large");
+  // (the input of so few pixels stays in L2: read once per block of output channels)
+  const Bytes b = module_bytes(g, g.ho, g.wo, p->co_block);
+  p->waves = 8;
+  p->depth = 0;
+  p->splits = 1;
+  p->lds_bytes = lds;
+  p->workgroups = (int32_t)wgs;
+  p->bytes_ideal = b.ideal;
+  p->bytes_tiled = b.tiled;
+  p->bytes_paper = b.paper;
+  p->redundancy = b.redundancy;
+  return FCM_OK;
+}
+
 fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, fcm_plan_t* p) {
   (void)d;
   int nv = 0;
@@ -468,6 +497,7 @@ fcm_status evaluate_plan(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
   if (v.gen == 4) return evaluate_plan4(v, g, hw, p);
   if (v.gen == 8) return evaluate_plan8(v, g, hw, p);
   if (v.gen == 9) return evaluate_plan9(v, g, hw, p);
+  if (v.gen == 10) return evaluate_plan10(v, g, hw, p);
   int depth = v.gen == 3 ? p->depth : 0;
   const int lds = tiling_lds(v, g, p->tile_h, p->tile_w, p->c_block, p->co_block, hw.lds_per_wg, &depth);
   if (lds <= 0) return fail(FCM_EUNSUPPORTED, "plan: tiling not implemented by the kernel variant");
@@ -865,6 +895,22 @@ static double dp_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t
   return kLaunch + one * std::max(1.0, 0.5 * share + 0.5 * std::ceil(share)) / kClock;
 }
 
+// Time model of the DW->PW kernels for few pixels (gen 10), in seconds: the launch, then
+// whole rounds of workgroups (more than one on a CU take turns at its address unit), each
+// a fixed part, the load instructions of every chunk (per pixel block the taps, per pixel
+// block and output tile the weights) and the chunks a wave filters one after another.
+// Fitted to 330 timed plans of 21 layers at batch 1 to 16: within 0.91-1.11x for 80% of
+// them; the margin keeps the other kernels at near ties, where they measured faster (16 x
+// 56x56x96 -> 24 stride 2 6.4 against 7.0 us, 8 x 28x28x192 -> 32 7.0 against 7.3).
+static double few_time_estimate(const Variant& v, const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
+  constexpr double kLaunch = 1.6e-6, kClock = 2.4e9, kStart = 3000.0, kBlock = 440.0, kTile = 81.0, kIter = 1235.0,
+                   kMargin = 1.12;
+  const int nch = ceil_div(g.ci, 32), tiles = std::min(v.max_cob, round_up(g.co, 16)) / 16;
+  const double rounds = std::ceil((double)p.workgroups / hw.num_cus);
+  return kMargin * (kLaunch + rounds * (kStart + nch * v.wc * (kBlock + kTile * tiles) +
+                                        kIter * ceil_div(nch, 8 / v.wc)) / kClock);
+}
+
 double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc& hw) {
   int nv = 0;
   const Variant* vs = all_variants(&nv);
@@ -876,6 +922,7 @@ double plan_time_estimate(const Geom& g, const fcm_plan_t& p, const fcm_hw_desc&
   if (v.gen == 7) return deep_time_estimate(v, g, p, hw);
   if (v.gen == 8) return ir_time_estimate(v, g, p, hw);
   if (v.gen == 9) return dp_time_estimate(v, g, p, hw);
+  if (v.gen == 10) return few_time_estimate(v, g, p, hw);
   // the register kernel's structural model ranks its own plans; for comparisons with other
   // kernels the fitted figure bounds it from below
   if (v.gen == 4) return std::max(pwpw4_time_estimate(v, g, p, hw), linear_time_estimate(v, g, p));
@@ -916,8 +963,8 @@ static void collect(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw, int
     const Variant& v = vs[vi];
     if (!variant_matches(v, g)) continue;
     if (!in_set(v, kset)) continue;
-    if (v.gen == 5 || v.gen == 7) {
-      // streaming and deep kernels: one compiled tile and output-channel block each
+    if (v.gen == 5 || v.gen == 7 || v.gen == 10) {
+      // streaming, deep and few-pixel kernels: one compiled tile and output-channel block each
       Cand c;
       memset(&c.p, 0, sizeof(c.p));
       c.p.op = g.op;
@@ -1098,6 +1145,9 @@ static fcm_status search(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
   const Variant* vs = all_variants(&nv);
   std::vector<Cand> cands;
   collect(g, d, hw, kset, ws_max, cands);
+  if (!(kset & KSET_FEW))
+    cands.erase(std::remove_if(cands.begin(), cands.end(), [&](const Cand& c) { return vs[c.p.variant].gen == 10; }),
+                cands.end());
   if (cands.empty()) return fail(FCM_EUNSUPPORTED, "plan: no compiled kernel implements this shape");
   // The PW -> PW register kernel (gen 4) is preferred wherever one implements the shape:
   // the plan with the least estimated time, ties to the smaller variant.
@@ -1118,14 +1168,15 @@ static fcm_status search(const Geom& g, const fcm_desc* d, const fcm_hw_desc& hw
     }
   }
   // The persistent (gen 3), streaming (gen 5), whole-module (gen 6), deep (gen 7),
-  // PW->DW(->PW) (gen 8) and NCHW DW->PW (gen 9) kernels are preferred wherever one implements the shape; among
-  // them the plan with the least estimated time under its kernel family's fitted model wins.
+  // PW->DW(->PW) (gen 8), NCHW (gen 9) and few-pixel DW->PW (gen 10) kernels are preferred
+  // wherever one implements the shape; among them the plan with the least estimated time
+  // under its kernel family's fitted model wins.
   {
     const Cand* best35 = nullptr;
     double best_t = 0;
     for (const Cand& c : cands) {
       const int gen = vs[c.p.variant].gen;
-      if (gen != 3 && gen != 5 && gen != 6 && gen != 7 && gen != 8 && gen != 9) continue;
+      if (gen != 3 && gen != 5 && gen != 6 && gen != 7 && gen != 8 && gen != 9 && gen != 10) continue;
       const double t = plan_time_estimate(g, c.p, hw);
       if (!best35 || t < best_t || (t == best_t && c.p.variant < best35->p.variant)) {
         best35 = &c;
